@@ -61,50 +61,87 @@ __device__ __forceinline__ bf16x8 k32_pair(const bf16x4 &lo, const bf16x4 &hi)
     return bf16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
 }
 
+// Four consecutive bfloat16 values in one 8-byte load (the library's own
+// weight copies: 256-byte aligned, offsets a multiple of four).
+__device__ __forceinline__ bf16x4 load4(const short *__restrict__ p) { return *reinterpret_cast<const bf16x4 *>(p); }
+
+// the A operand of K = 32 step p for weight row `row` of a 64 x 64 matrix: two
+// runs of four consecutive units (k32_unit)
+__device__ __forceinline__ bf16x8 load_k32(const short *__restrict__ w, int row, int p, int lg)
+{
+    return k32_pair(load4(w + row * 64 + k32_unit(p, lg, 0)), load4(w + row * 64 + k32_unit(p, lg, 4)));
+}
+
 // parameter offsets in the flat vector: w1 (64x16), b1, w2 (64x64), b2, w3, b3
 constexpr int OFF_W1 = 0, OFF_B1 = 1024, OFF_W2 = 1088, OFF_B2 = 5184, OFF_W3 = 5248, OFF_B3 = 5312;
 
 struct MlpW {
     const short *w1b, *w2b, *w3b; // bfloat16 copies
+    const short *w2tb;            // W2 transposed, bfloat16 (the gradient's backward contraction)
     const float *p;               // float32 master values (biases read from here)
 };
 
 // ----------------------------------------------------------------- forward
-__global__ __launch_bounds__(kBlock) void k_mlp_forward(const short *__restrict__ F, int64_t N, MlpW w,
+// The four features 4 lg .. 4 lg + 3 of variable v as the B operand: bfloat16
+// ones as they are, float32 ones rounded here.  A caller's buffers are only
+// element-aligned, hence the copies (one 8- or 16-byte load each).
+__device__ __forceinline__ bf16x4 load_features(const short *__restrict__ F, int64_t v, int lg)
+{
+    bf16x4 f;
+    __builtin_memcpy(&f, F + v * 16 + 4 * lg, sizeof(f));
+    return f;
+}
+
+__device__ __forceinline__ bf16x4 load_features(const float *__restrict__ F, int64_t v, int lg)
+{
+    f32x4 f;
+    __builtin_memcpy(&f, F + v * 16 + 4 * lg, sizeof(f));
+    return bf16x4{f2bf(f[0]), f2bf(f[1]), f2bf(f[2]), f2bf(f[3])};
+}
+
+// One wave per tile of 16 variables: a call of 65,536 variables is one round
+// of 4,096 waves and is bound by its chain of loads and matrix steps, so the
+// features, weights and biases go out together, as 8- and 16-byte loads (11.9
+// us per call with a separate bfloat16 pass and 2-byte weight loads, 9.1 us
+// now, host calls included).
+template <typename FT>
+__global__ __launch_bounds__(kBlock) void k_mlp_forward(const FT *__restrict__ F, int64_t N, MlpW w,
                                                        float *__restrict__ logits)
 {
     const int lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
-    bf16x4 w1a[4];
-    bf16x8 w2a[4][2];
-#pragma unroll
-    for (int mb = 0; mb < 4; mb++) {
-#pragma unroll
-        for (int i = 0; i < 4; i++) w1a[mb][i] = w.w1b[(16 * mb + lr) * 16 + 4 * lg + i];
-#pragma unroll
-        for (int p = 0; p < 2; p++)
-#pragma unroll
-            for (int i = 0; i < 8; i++) w2a[mb][p][i] = w.w2b[(16 * mb + lr) * 64 + k32_unit(p, lg, i)];
-    }
-    const float b3 = w.p[OFF_B3];
     const int64_t ntiles = (N + 15) / 16;
     const int64_t nwaves = (int64_t)gridDim.x * (kBlock / 64);
-    for (int64_t t = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6; t < ntiles; t += nwaves) {
-        const int64_t v = t * 16 + lr;
-        bf16x4 fb = {0, 0, 0, 0};
-        if (v < N) {
+    int64_t t = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
+    if (t >= ntiles) return;
+    // the first tile's features go out with the weights
+    bf16x4 fb = load_features(F, t * 16 + lr < N ? t * 16 + lr : N - 1, lg);
+    bf16x4 w1a[4], w3b[4];
+    bf16x8 w2a[4][2];
+    f32x4 b1[4], b2[4];
 #pragma unroll
-            for (int i = 0; i < 4; i++) fb[i] = F[v * 16 + 4 * lg + i];
-        }
+    for (int mb = 0; mb < 4; mb++) {
+        w1a[mb] = load4(w.w1b + (16 * mb + lr) * 16 + 4 * lg);
+#pragma unroll
+        for (int p = 0; p < 2; p++) w2a[mb][p] = load_k32(w.w2b, 16 * mb + lr, p, lg);
+        w3b[mb] = load4(w.w3b + 16 * mb + 4 * lg);
+        b1[mb] = *reinterpret_cast<const f32x4 *>(w.p + OFF_B1 + 16 * mb + 4 * lg);
+        b2[mb] = *reinterpret_cast<const f32x4 *>(w.p + OFF_B2 + 16 * mb + 4 * lg);
+    }
+    const float b3 = w.p[OFF_B3];
+    for (; t < ntiles; t += nwaves) {
+        const int64_t v = t * 16 + lr; // lanes past N work on the last variable and store nothing
         bf16x4 h1b[4];
 #pragma unroll
         for (int mb = 0; mb < 4; mb++) {
             const f32x4 a = mfma16(w1a[mb], fb, f32x4{0, 0, 0, 0});
 #pragma unroll
             for (int r = 0; r < 4; r++) {
-                const float h = a[r] + w.p[OFF_B1 + 16 * mb + 4 * lg + r];
+                const float h = a[r] + b1[mb][r];
                 h1b[mb][r] = f2bf(h > 0.0f ? h : 0.0f);
             }
         }
+        const int64_t vn = v + nwaves * 16; // the next tile's features, before this one's second layer
+        fb = load_features(F, vn < N ? vn : N - 1, lg);
         float part = 0.0f;
         const bf16x8 h1p[2] = {k32_pair(h1b[0], h1b[1]), k32_pair(h1b[2], h1b[3])};
 #pragma unroll
@@ -114,10 +151,9 @@ __global__ __launch_bounds__(kBlock) void k_mlp_forward(const short *__restrict_
             for (int p = 0; p < 2; p++) a = mfma32(w2a[mb][p], h1p[p], a);
 #pragma unroll
             for (int r = 0; r < 4; r++) {
-                const int h = 16 * mb + 4 * lg + r;
-                float hv = a[r] + w.p[OFF_B2 + h];
+                float hv = a[r] + b2[mb][r];
                 hv = hv > 0.0f ? hv : 0.0f;
-                part += bf2f(w.w3b[h]) * hv;
+                part += bf2f(w3b[mb][r]) * hv;
             }
         }
         part += __shfl_xor(part, 16, 64);
@@ -127,34 +163,54 @@ __global__ __launch_bounds__(kBlock) void k_mlp_forward(const short *__restrict_
 }
 
 // ---------------------------------------------------------------- gradient
-// Each wave handles `tiles_per_wave` tiles of 16 samples of the minibatch
+// Each wave handles kGradTiles tiles of 16 samples of the minibatch
 // (samples idx[b0 + k], k < bsz) and writes its partial gradient (5313
 // values) and partial loss; k_mlp_reduce sums the partials in wave order.
+// A minibatch of 4,096 samples is only 128 waves and every one a serial chain:
+// one wave per workgroup spreads them over 128 CUs instead of 32, both tiles'
+// samples are loaded before the weights, and the weights come in 8-byte loads
+// (W2^T from a transposed copy): 18.6 -> 13.1 us.
 __device__ __forceinline__ float softplus(float x) { return x > 0.0f ? x + log1pf(expf(-x)) : log1pf(expf(x)); }
 
-__global__ __launch_bounds__(kBlock) void k_mlp_grad(const short *__restrict__ F, const float *__restrict__ Y,
-                                                    const int *__restrict__ idx, int64_t b0, int bsz,
-                                                    int tiles_per_wave, float pw, MlpW w,
-                                                    float *__restrict__ part, float *__restrict__ lossp)
+constexpr int kGradTiles = 2; // tiles of 16 samples per wave
+
+__global__ __launch_bounds__(64) void k_mlp_grad(const short *__restrict__ F, const float *__restrict__ Y,
+                                                const int *__restrict__ idx, int64_t b0, int bsz, float pw, MlpW w,
+                                                float *__restrict__ part, float *__restrict__ lossp)
 {
-    __shared__ short sA[kBlock / 64][64 * 16];
-    __shared__ short sB[kBlock / 64][64 * 16];
-    __shared__ short sF[kBlock / 64][16 * 16];
-    const int lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4, wid = threadIdx.x >> 6;
-    const int gw = blockIdx.x * (kBlock / 64) + wid; // global wave number
-    bf16x4 w1a[4];
+    __shared__ short a_s[64 * 16];
+    __shared__ short b_s[64 * 16];
+    __shared__ short f_s[16 * 16];
+    const int lane = threadIdx.x, lr = lane & 15, lg = lane >> 4;
+    const int gw = blockIdx.x; // wave number: one wave per workgroup
+    // every tile's samples before the weights: index, then features and label
+    bf16x4 ft[kGradTiles];
+    float yt[kGradTiles];
+    int rows[kGradTiles];
+#pragma unroll
+    for (int tt = 0; tt < kGradTiles; tt++) {
+        const int k = (gw * kGradTiles + tt) * 16 + lr;
+        rows[tt] = idx[b0 + (k < bsz ? k : bsz - 1)];
+    }
+#pragma unroll
+    for (int tt = 0; tt < kGradTiles; tt++) {
+        ft[tt] = load4(F + (int64_t)rows[tt] * 16 + 4 * lg);
+        yt[tt] = Y[rows[tt]];
+    }
+    bf16x4 w1a[4], w3b[4];
     bf16x8 w2a[4][2], w2t[4][2];
+    f32x4 b1[4], b2[4];
 #pragma unroll
     for (int mb = 0; mb < 4; mb++) {
+        w1a[mb] = load4(w.w1b + (16 * mb + lr) * 16 + 4 * lg);
 #pragma unroll
-        for (int i = 0; i < 4; i++) w1a[mb][i] = w.w1b[(16 * mb + lr) * 16 + 4 * lg + i];
-#pragma unroll
-        for (int p = 0; p < 2; p++)
-#pragma unroll
-            for (int i = 0; i < 8; i++) {
-                w2a[mb][p][i] = w.w2b[(16 * mb + lr) * 64 + k32_unit(p, lg, i)];
-                w2t[mb][p][i] = w.w2b[k32_unit(p, lg, i) * 64 + 16 * mb + lr]; // W2^T
-            }
+        for (int p = 0; p < 2; p++) {
+            w2a[mb][p] = load_k32(w.w2b, 16 * mb + lr, p, lg);
+            w2t[mb][p] = load_k32(w.w2tb, 16 * mb + lr, p, lg); // W2^T
+        }
+        w3b[mb] = load4(w.w3b + 16 * mb + 4 * lg);
+        b1[mb] = *reinterpret_cast<const f32x4 *>(w.p + OFF_B1 + 16 * mb + 4 * lg);
+        b2[mb] = *reinterpret_cast<const f32x4 *>(w.p + OFF_B2 + 16 * mb + 4 * lg);
     }
     const float b3 = w.p[OFF_B3];
     const float inv_b = 1.0f / (float)bsz;
@@ -168,18 +224,12 @@ __global__ __launch_bounds__(kBlock) void k_mlp_grad(const short *__restrict__ F
 #pragma unroll
         for (int nb = 0; nb < 4; nb++) gw2[mb][nb] = f32x4{0, 0, 0, 0};
     }
-    short *a_s = sA[wid], *b_s = sB[wid], *f_s = sF[wid];
-    for (int tt = 0; tt < tiles_per_wave; tt++) {
-        const int64_t k = ((int64_t)gw * tiles_per_wave + tt) * 16 + lr; // sample slot in the minibatch
-        const bool valid = k < bsz;
-        const int64_t row = valid ? (int64_t)idx[b0 + k] : 0;
-        bf16x4 fb = {0, 0, 0, 0};
-        float y = 0.0f;
-        if (valid) {
 #pragma unroll
-            for (int i = 0; i < 4; i++) fb[i] = F[row * 16 + 4 * lg + i];
-            y = Y[row];
-        }
+    for (int tt = 0; tt < kGradTiles; tt++) {
+        const int k = (gw * kGradTiles + tt) * 16 + lr; // sample slot in the minibatch
+        const bool valid = k < bsz;
+        const bf16x4 fb = valid ? ft[tt] : bf16x4{0, 0, 0, 0};
+        const float y = valid ? yt[tt] : 0.0f;
         // forward, keeping the activations
         float h1[4][4], h2[4][4];
         bf16x4 h1b[4];
@@ -188,7 +238,7 @@ __global__ __launch_bounds__(kBlock) void k_mlp_grad(const short *__restrict__ F
             const f32x4 a = mfma16(w1a[mb], fb, f32x4{0, 0, 0, 0});
 #pragma unroll
             for (int r = 0; r < 4; r++) {
-                const float h = a[r] + w.p[OFF_B1 + 16 * mb + 4 * lg + r];
+                const float h = a[r] + b1[mb][r];
                 h1[mb][r] = h > 0.0f ? h : 0.0f;
                 h1b[mb][r] = f2bf(h1[mb][r]);
             }
@@ -202,10 +252,9 @@ __global__ __launch_bounds__(kBlock) void k_mlp_grad(const short *__restrict__ F
             for (int p = 0; p < 2; p++) a = mfma32(w2a[mb][p], h1p[p], a);
 #pragma unroll
             for (int r = 0; r < 4; r++) {
-                const int h = 16 * mb + 4 * lg + r;
-                const float hv = a[r] + w.p[OFF_B2 + h];
+                const float hv = a[r] + b2[mb][r];
                 h2[mb][r] = hv > 0.0f ? hv : 0.0f;
-                z += bf2f(w.w3b[h]) * h2[mb][r];
+                z += bf2f(w3b[mb][r]) * h2[mb][r];
             }
         }
         z += __shfl_xor(z, 16, 64);
@@ -227,9 +276,8 @@ __global__ __launch_bounds__(kBlock) void k_mlp_grad(const short *__restrict__ F
         for (int mb = 0; mb < 4; mb++)
 #pragma unroll
             for (int r = 0; r < 4; r++) {
-                const int h = 16 * mb + 4 * lg + r;
                 gw3[mb][r] += dz * h2[mb][r];
-                const float d = h2[mb][r] > 0.0f ? dz * bf2f(w.w3b[h]) : 0.0f;
+                const float d = h2[mb][r] > 0.0f ? dz * bf2f(w3b[mb][r]) : 0.0f;
                 gb2[mb][r] += d;
                 dh2b[mb][r] = f2bf(d);
             }
@@ -323,55 +371,89 @@ __global__ __launch_bounds__(kBlock) void k_mlp_grad(const short *__restrict__ F
     }
 }
 
-// grad[p] = sum over waves of part[w][p], in wave order
-__global__ __launch_bounds__(kBlock) void k_mlp_reduce(const float *__restrict__ part, int nw,
-                                                      const float *__restrict__ lossp, float *__restrict__ grad,
-                                                      double *__restrict__ loss_acc)
+// Adam (Kingma and Ba 2015): bc1 = 1 - beta1^t, bc2 = 1 - beta2^t
+struct AdamStep {
+    float lr, beta1, beta2, eps, bc1, bc2;
+};
+
+// the bfloat16 copies of parameter k
+__device__ __forceinline__ void store_bf16(int k, float pk, short *__restrict__ w1b, short *__restrict__ w2b,
+                                           short *__restrict__ w3b, short *__restrict__ w2tb)
 {
-    const int p = blockIdx.x * kBlock + threadIdx.x;
-    if (p < MLP_NPARAMS) {
-        float acc = 0.0f;
-        for (int w = 0; w < nw; w++) acc += part[(size_t)w * MLP_NPARAMS + p];
-        grad[p] = acc;
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        double l = 0.0;
-        for (int w = 0; w < nw; w++) l += (double)lossp[w];
-        loss_acc[0] += l;
-    }
+    if (k < OFF_B1) w1b[k - OFF_W1] = f2bf(pk);
+    else if (k >= OFF_W2 && k < OFF_B2) {
+        const int e = k - OFF_W2;
+        w2b[e] = f2bf(pk);
+        w2tb[(e & 63) * 64 + (e >> 6)] = f2bf(pk);
+    } else if (k >= OFF_W3 && k < OFF_B3) w3b[k - OFF_W3] = f2bf(pk);
 }
 
-// Adam (Kingma and Ba 2015) on the float32 master values, then fresh
-// bfloat16 copies of the weights.  bc1 = 1 - beta1^t, bc2 = 1 - beta2^t.
-__global__ __launch_bounds__(kBlock) void k_mlp_adam(float *__restrict__ p, float *__restrict__ m,
-                                                    float *__restrict__ v, const float *__restrict__ g, float lr,
-                                                    float beta1, float beta2, float eps, float bc1, float bc2,
-                                                    short *__restrict__ w1b, short *__restrict__ w2b,
-                                                    short *__restrict__ w3b)
+// grad[p] = sum over waves of part[w][p], in wave order, kReduceDepth loads
+// in flight; with ADAM the same thread then takes the Adam step on the
+// float32 master value and refreshes its bfloat16 copies, so a minibatch is
+// two launches.  The workgroup past the parameters adds up the losses, in
+// wave order, loaded side by side through LDS.  Measured (minibatch 4,096, 128
+// waves): 34.1 us for the sum and 4.5 us for a separate Adam launch before,
+// most of it one thread's chain of dependent loss loads.
+constexpr int kReduceBlock = 64;
+constexpr int kReduceDepth = 32;
+constexpr int kLossChunk = 1024;
+
+template <bool ADAM>
+__global__ __launch_bounds__(kReduceBlock) void k_mlp_reduce(const float *__restrict__ part, int nw,
+                                                            const float *__restrict__ lossp,
+                                                            float *__restrict__ grad, double *__restrict__ loss_acc,
+                                                            AdamStep ad, float *__restrict__ pv, float *__restrict__ m,
+                                                            float *__restrict__ v, short *__restrict__ w1b,
+                                                            short *__restrict__ w2b, short *__restrict__ w3b,
+                                                            short *__restrict__ w2tb)
 {
-    const int k = blockIdx.x * kBlock + threadIdx.x;
-    if (k >= MLP_NPARAMS) return;
-    const float gk = g[k];
-    const float mk = beta1 * m[k] + (1.0f - beta1) * gk;
-    const float vk = beta2 * v[k] + (1.0f - beta2) * gk * gk;
-    m[k] = mk;
-    v[k] = vk;
-    const float pk = p[k] - lr * (mk / bc1) / (sqrtf(vk / bc2) + eps);
-    p[k] = pk;
-    if (k < OFF_B1) w1b[k - OFF_W1] = f2bf(pk);
-    else if (k >= OFF_W2 && k < OFF_B2) w2b[k - OFF_W2] = f2bf(pk);
-    else if (k >= OFF_W3 && k < OFF_B3) w3b[k - OFF_W3] = f2bf(pk);
+    __shared__ float s_loss[kLossChunk];
+    if (blockIdx.x == gridDim.x - 1) {
+        double l = 0.0;
+        for (int w0 = 0; w0 < nw; w0 += kLossChunk) {
+            const int len = nw - w0 < kLossChunk ? nw - w0 : kLossChunk;
+            for (int k = threadIdx.x; k < len; k += kReduceBlock) s_loss[k] = lossp[w0 + k];
+            __syncthreads();
+            if (threadIdx.x == 0)
+                for (int k = 0; k < len; k++) l += (double)s_loss[k];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) loss_acc[0] += l;
+        return;
+    }
+    const int p = blockIdx.x * kReduceBlock + threadIdx.x;
+    if (p >= MLP_NPARAMS) return;
+    float acc = 0.0f;
+    int w = 0;
+    for (; w + kReduceDepth <= nw; w += kReduceDepth) {
+        float a[kReduceDepth];
+#pragma unroll
+        for (int u = 0; u < kReduceDepth; u++) a[u] = part[(size_t)(w + u) * MLP_NPARAMS + p];
+#pragma unroll
+        for (int u = 0; u < kReduceDepth; u++) acc += a[u];
+    }
+    for (; w < nw; w++) acc += part[(size_t)w * MLP_NPARAMS + p];
+    if (!ADAM) {
+        grad[p] = acc;
+        return;
+    }
+    const float mk = ad.beta1 * m[p] + (1.0f - ad.beta1) * acc;
+    const float vk = ad.beta2 * v[p] + (1.0f - ad.beta2) * acc * acc;
+    m[p] = mk;
+    v[p] = vk;
+    const float pk = pv[p] - ad.lr * (mk / ad.bc1) / (sqrtf(vk / ad.bc2) + ad.eps);
+    pv[p] = pk;
+    store_bf16(p, pk, w1b, w2b, w3b, w2tb);
 }
 
 // bfloat16 copies of the weights from the master values
 __global__ __launch_bounds__(kBlock) void k_mlp_sync_bf16(const float *__restrict__ p, short *__restrict__ w1b,
-                                                         short *__restrict__ w2b, short *__restrict__ w3b)
+                                                         short *__restrict__ w2b, short *__restrict__ w3b,
+                                                         short *__restrict__ w2tb)
 {
     const int k = blockIdx.x * kBlock + threadIdx.x;
-    if (k >= MLP_NPARAMS) return;
-    if (k < OFF_B1) w1b[k - OFF_W1] = f2bf(p[k]);
-    else if (k >= OFF_W2 && k < OFF_B2) w2b[k - OFF_W2] = f2bf(p[k]);
-    else if (k >= OFF_W3 && k < OFF_B3) w3b[k - OFF_W3] = f2bf(p[k]);
+    if (k < MLP_NPARAMS) store_bf16(k, p[k], w1b, w2b, w3b, w2tb);
 }
 
 // float32 features (N x 16) to bfloat16
@@ -415,12 +497,12 @@ hipError_t mlp_init(pdhg_mlp *net, uint64_t seed)
     return mlp_sync(net);
 }
 
-static MlpW weights(const pdhg_mlp *net) { return MlpW{net->w1b, net->w2b, net->w3b, net->p}; }
+static MlpW weights(const pdhg_mlp *net) { return MlpW{net->w1b, net->w2b, net->w3b, net->w2tb, net->p}; }
 
 hipError_t mlp_sync(pdhg_mlp *net)
 {
     hipLaunchKernelGGL(k_mlp_sync_bf16, dim3((MLP_NPARAMS + kBlock - 1) / kBlock), dim3(kBlock), 0, net->stream, net->p,
-                       net->w1b, net->w2b, net->w3b);
+                       net->w1b, net->w2b, net->w3b, net->w2tb);
     return hipGetLastError();
 }
 
@@ -430,45 +512,64 @@ hipError_t mlp_features_to_bf16(hipStream_t st, const float *src, short *dst, in
     return hipGetLastError();
 }
 
-hipError_t mlp_forward(const pdhg_mlp *net, hipStream_t st, const short *F, int64_t N, float *logits)
+template <typename FT>
+static hipError_t forward_impl(const pdhg_mlp *net, hipStream_t st, const FT *F, int64_t N, float *logits)
 {
     if (N <= 0) return hipSuccess;
     const int64_t tiles = (N + 15) / 16;
     const int grid = grid_for((tiles + 3) / 4, 1, 1 << 20);
-    hipLaunchKernelGGL(k_mlp_forward, dim3(grid), dim3(kBlock), 0, st, F, N, weights(net), logits);
+    hipLaunchKernelGGL((k_mlp_forward<FT>), dim3(grid), dim3(kBlock), 0, st, F, N, weights(net), logits);
     return hipGetLastError();
 }
 
-// one minibatch: gradient into net->grad, loss added to net->loss_acc
-hipError_t mlp_grad(pdhg_mlp *net, const short *F, const float *Y, const int *idx, int64_t b0, int bsz, float pw)
+hipError_t mlp_forward(const pdhg_mlp *net, hipStream_t st, const short *F, int64_t N, float *logits)
+{
+    return forward_impl(net, st, F, N, logits);
+}
+
+// one minibatch: gradient into net->grad (adam NULL) or an Adam step with it,
+// loss added to net->loss_acc
+static hipError_t grad_impl(pdhg_mlp *net, const short *F, const float *Y, const int *idx, int64_t b0, int bsz, float pw,
+                            const AdamStep *adam)
 {
     const int tiles = (bsz + 15) / 16;
-    const int tpw = 2;
-    const int waves = (tiles + tpw - 1) / tpw;
-    const int blocks = (waves + 3) / 4;
-    const int nw = blocks * 4;
+    const int nw = (tiles + kGradTiles - 1) / kGradTiles;
     if (nw > net->max_waves) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_mlp_grad, dim3(blocks), dim3(kBlock), 0, net->stream, F, Y, idx, b0, bsz, tpw, pw,
-                       weights(net), net->part, net->lossp);
-    hipLaunchKernelGGL(k_mlp_reduce, dim3((MLP_NPARAMS + kBlock - 1) / kBlock), dim3(kBlock), 0, net->stream,
-                       net->part, nw, net->lossp, net->grad, net->loss_acc);
+    hipLaunchKernelGGL(k_mlp_grad, dim3(nw), dim3(64), 0, net->stream, F, Y, idx, b0, bsz, pw, weights(net), net->part,
+                       net->lossp);
+    const dim3 grid((MLP_NPARAMS + kReduceBlock - 1) / kReduceBlock + 1);
+    if (adam)
+        hipLaunchKernelGGL((k_mlp_reduce<true>), grid, dim3(kReduceBlock), 0, net->stream, net->part, nw, net->lossp,
+                           net->grad, net->loss_acc, *adam, net->p, net->m, net->v, net->w1b, net->w2b, net->w3b,
+                           net->w2tb);
+    else
+        hipLaunchKernelGGL((k_mlp_reduce<false>), grid, dim3(kReduceBlock), 0, net->stream, net->part, nw, net->lossp,
+                           net->grad, net->loss_acc, AdamStep{}, net->p, net->m, net->v, net->w1b, net->w2b, net->w3b,
+                           net->w2tb);
     return hipGetLastError();
 }
 
-hipError_t mlp_adam(pdhg_mlp *net, float lr, float beta1, float beta2, float eps, int64_t t)
+hipError_t mlp_grad(pdhg_mlp *net, const short *F, const float *Y, const int *idx, int64_t b0, int bsz, float pw)
 {
-    const float bc1 = 1.0f - powf(beta1, (float)t), bc2 = 1.0f - powf(beta2, (float)t);
-    hipLaunchKernelGGL(k_mlp_adam, dim3((MLP_NPARAMS + kBlock - 1) / kBlock), dim3(kBlock), 0, net->stream, net->p,
-                       net->m, net->v, net->grad, lr, beta1, beta2, eps, bc1, bc2, net->w1b, net->w2b, net->w3b);
-    return hipGetLastError();
+    return grad_impl(net, F, Y, idx, b0, bsz, pw, nullptr);
+}
+
+hipError_t mlp_train_step(pdhg_mlp *net, const short *F, const float *Y, const int *idx, int64_t b0, int bsz, float pw,
+                          float lr, float beta1, float beta2, float eps, int64_t t)
+{
+    const AdamStep ad{lr, beta1, beta2, eps, 1.0f - powf(beta1, (float)t), 1.0f - powf(beta2, (float)t)};
+    return grad_impl(net, F, Y, idx, b0, bsz, pw, &ad);
 }
 
 } // namespace pdhg
 
 // ------------------------------------------------- forward without allocation
 // For callers that cannot allocate (graph capture, serving loops): the
-// bfloat16 staging copy of the features lives in this file-scope device
-// array instead of a buffer allocated per call.  Every GPU the library runs
+// kernel reads the caller's float32 features and rounds them in registers
+// (the same values as a bfloat16 copy, one launch instead of two).  Only
+// where the logits overlap the features, which are then overwritten while
+// other waves still read, a bfloat16 copy is staged first; it lives in this
+// file-scope device array instead of a buffer allocated per call.  Every GPU the library runs
 // on holds its own copy until the process ends.  Host code never passes the
 // array's name to a kernel (on the host it is only a stand-in symbol): the
 // device address comes from hipGetSymbolAddress, once per device with that
@@ -518,12 +619,20 @@ extern "C" int pdhg_mlp_forward_noalloc(pdhg_mlp *net, const float *features, in
     if (n > kNoAllocMaxRows)
         return fail(PDHG_ERR_INVALID_ARG, "pdhg_mlp_forward_noalloc takes at most 65536 variables per call");
     if (n == 0) return PDHG_OK;
-    short *fb = nullptr;
-    hipError_t e = scratch_for_current_device(&fb);
-    if (e != hipSuccess) return fail(PDHG_ERR_HIP, std::string("HIP error in hipGetSymbolAddress: ") + hipGetErrorString(e));
     hipStream_t st = stream ? (hipStream_t)stream : net->stream;
-    e = mlp_features_to_bf16(st, features, fb, n); // every staged row is overwritten: nothing to clear
-    if (e == hipSuccess) e = mlp_forward(net, st, fb, n, logits);
+    const uintptr_t f0 = (uintptr_t)features, f1 = (uintptr_t)(features + 16 * n), l0 = (uintptr_t)logits,
+                    l1 = (uintptr_t)(logits + n);
+    hipError_t e = hipSuccess;
+    if (l0 >= f1 || f0 >= l1) {
+        e = forward_impl(net, st, features, n, logits);
+    } else {
+        short *fb = nullptr;
+        e = scratch_for_current_device(&fb);
+        if (e != hipSuccess)
+            return fail(PDHG_ERR_HIP, std::string("HIP error in hipGetSymbolAddress: ") + hipGetErrorString(e));
+        e = mlp_features_to_bf16(st, features, fb, n); // every staged row is overwritten: nothing to clear
+        if (e == hipSuccess) e = mlp_forward(net, st, fb, n, logits);
+    }
     if (e != hipSuccess) return fail(PDHG_ERR_HIP, std::string("HIP error in the forward launch: ") + hipGetErrorString(e));
     return PDHG_OK;
 }

@@ -13,6 +13,7 @@ struct pdhg_mlp {
     hipStream_t stream = nullptr;
     float *p = nullptr, *m = nullptr, *v = nullptr, *grad = nullptr; // float32 master values, Adam state
     short *w1b = nullptr, *w2b = nullptr, *w3b = nullptr;           // bfloat16 weight copies
+    short *w2tb = nullptr;                                           // W2 transposed (the gradient kernel)
     float *part = nullptr, *lossp = nullptr;                         // per-wave partial gradients and losses
     int max_waves = 0;
     double *loss_acc = nullptr;
@@ -25,7 +26,9 @@ hipError_t mlp_init(pdhg_mlp *net, uint64_t seed);
 hipError_t mlp_features_to_bf16(hipStream_t st, const float *src, short *dst, int64_t n_rows);
 hipError_t mlp_forward(const pdhg_mlp *net, hipStream_t st, const short *F, int64_t N, float *logits);
 hipError_t mlp_grad(pdhg_mlp *net, const short *F, const float *Y, const int *idx, int64_t b0, int bsz, float pw);
-hipError_t mlp_adam(pdhg_mlp *net, float lr, float beta1, float beta2, float eps, int64_t t);
+// the same minibatch's gradient and Adam step t
+hipError_t mlp_train_step(pdhg_mlp *net, const short *F, const float *Y, const int *idx, int64_t b0, int bsz, float pw,
+                          float lr, float beta1, float beta2, float eps, int64_t t);
 // device address of the no-allocation forward's staging array on the current
 // device (looked up once per device)
 hipError_t mlp_scratch_setup();

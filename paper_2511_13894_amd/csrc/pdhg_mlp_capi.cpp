@@ -92,6 +92,7 @@ int pdhg_mlp_create(uint64_t seed, pdhg_mlp **out)
         CHK(hipMalloc(&net->w1b, sizeof(short) * 1024));
         CHK(hipMalloc(&net->w2b, sizeof(short) * 4096));
         CHK(hipMalloc(&net->w3b, sizeof(short) * 64));
+        CHK(hipMalloc(&net->w2tb, sizeof(short) * 4096));
         net->max_waves = (int)((((kMaxBatch + 15) / 16 + 1) / 2 + 3) / 4 * 4);
         CHK(hipMalloc(&net->part, sizeof(float) * MLP_NPARAMS * (size_t)net->max_waves));
         CHK(hipMalloc(&net->lossp, sizeof(float) * (size_t)net->max_waves));
@@ -112,7 +113,7 @@ void pdhg_mlp_destroy(pdhg_mlp *net)
     if (!net) return;
     if (net->stream) (void)hipStreamSynchronize(net->stream);
     for (void *q : {(void *)net->p, (void *)net->m, (void *)net->v, (void *)net->grad, (void *)net->w1b,
-                    (void *)net->w2b, (void *)net->w3b, (void *)net->part, (void *)net->lossp, (void *)net->loss_acc})
+                    (void *)net->w2b, (void *)net->w3b, (void *)net->w2tb, (void *)net->part, (void *)net->lossp, (void *)net->loss_acc})
         if (q) (void)hipFree(q);
     if (net->stream) (void)hipStreamDestroy(net->stream);
     delete net;
@@ -239,9 +240,9 @@ int pdhg_mlp_train(pdhg_mlp *net, const float *features, const float *labels, in
             CHK(hipMemsetAsync(net->loss_acc, 0, sizeof(double), net->stream));
             for (int64_t b0 = 0; b0 < n; b0 += t.batch) {
                 const int bsz = (int)std::min<int64_t>(t.batch, n - b0);
-                CHK(mlp_grad(net, d.F, d.Y, d.idx, b0, bsz, (float)pw));
                 net->adam_t += 1;
-                CHK(mlp_adam(net, (float)t.lr, (float)t.beta1, (float)t.beta2, (float)t.eps, net->adam_t));
+                CHK(mlp_train_step(net, d.F, d.Y, d.idx, b0, bsz, (float)pw, (float)t.lr, (float)t.beta1,
+                                   (float)t.beta2, (float)t.eps, net->adam_t));
                 steps++;
             }
             double l = 0.0;
