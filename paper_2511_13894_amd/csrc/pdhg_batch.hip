@@ -47,9 +47,10 @@ __global__ __launch_bounds__(NT) void kb_primal(const int4 *__restrict__ tiles, 
         lo = (double)lh[j];
         hi = (double)uh[j];
     }
+    const StepScalars sc = step_scalars(st, i);
     tile_row_sums<V, double, T, NT>(r0, rows, tp, ti, atv, y, s_ptr, s_prod, s_sum);
     if (!mine) return;
-    primal_update<V>(j, s_sum[tid], xj, cj, lo, hi, aj, x, xbar, xp, st, i, store_cand);
+    primal_update<V>(j, s_sum[tid], xj, cj, lo, hi, aj, x, xbar, xp, sc, store_cand);
 }
 
 template <typename V, int T, int NT>
@@ -78,9 +79,10 @@ __global__ __launch_bounds__(NT) void kb_dual(const int4 *__restrict__ tiles, co
         ar = ya[r];
         sn = sense[r];
     }
+    const StepScalars sc = step_scalars(st, i);
     tile_row_sums<V, V, T, NT>(r0, rows, rp, ci, av, xbar, s_ptr, s_prod, s_sum);
     if (!mine) return;
-    dual_update(r, s_sum[tid], yr, br, ar, sn, y, yp, st, i, store_cand);
+    dual_update(r, s_sum[tid], yr, br, ar, sn, y, yp, sc, store_cand);
 }
 
 template <typename V>

@@ -10,30 +10,64 @@
 
 namespace pdhg {
 
-// Sum over a group of L consecutive lanes (L a power of two <= 64); every lane
-// of the group ends with the group's sum.  Butterfly order is fixed, so the
-// result is deterministic.
+// The value `off` lanes up (off a power of two), for the lanes that a
+// reduction towards the lowest lane of an aligned group of 2 off lanes uses;
+// the others get something unspecified.  Register moves (DPP within a row of
+// 16 lanes, the row and half swaps across rows) instead of __shfl_xor's trips
+// through the LDS unit: a tree over 64 lanes has six of them in a row, and the
+// kernels that use it are bound by such chains (with the step scalars formed
+// early, pdhg_kernels.hpp: 4-6% of a step on LPs of up to 240,000 entries).
+template <int off>
+__device__ __forceinline__ int lane_up(int v)
+{
+    static_assert(off == 1 || off == 2 || off == 4 || off == 8 || off == 16 || off == 32, "a step of a tree over 64 lanes");
+    if constexpr (off == 32) return (int)__builtin_amdgcn_permlane32_swap(v, v, false, false)[1];
+    else if constexpr (off == 16) return (int)__builtin_amdgcn_permlane16_swap(v, v, false, false)[1];
+    else return __builtin_amdgcn_update_dpp(0, v, 0x100 + off, 0xf, 0xf, true); // row_shl: lane i reads lane i + off
+}
+
+template <int off>
+__device__ __forceinline__ float lane_up(float v)
+{
+    return __int_as_float(lane_up<off>(__float_as_int(v)));
+}
+
+template <int off>
+__device__ __forceinline__ double lane_up(double v)
+{
+    return __hiloint2double(lane_up<off>(__double2hiint(v)), lane_up<off>(__double2loint(v)));
+}
+
+// Sum over a group of L consecutive lanes (L a power of two <= 64), in the
+// group's lowest lane, by a fixed tree (halves added pairwise), so the result
+// is deterministic.
 template <int L, typename T>
 __device__ __forceinline__ T group_sum(T v)
 {
-#pragma unroll
-    for (int off = L / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, L);
+    if constexpr (L > 32) v += lane_up<32>(v);
+    if constexpr (L > 16) v += lane_up<16>(v);
+    if constexpr (L > 8) v += lane_up<8>(v);
+    if constexpr (L > 4) v += lane_up<4>(v);
+    if constexpr (L > 2) v += lane_up<2>(v);
+    if constexpr (L > 1) v += lane_up<1>(v);
     return v;
 }
 
-__device__ __forceinline__ double wave_sum(double v)
+template <int L>
+__device__ __forceinline__ double group_max(double v)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    if constexpr (L > 32) v = fmax(v, lane_up<32>(v));
+    if constexpr (L > 16) v = fmax(v, lane_up<16>(v));
+    if constexpr (L > 8) v = fmax(v, lane_up<8>(v));
+    if constexpr (L > 4) v = fmax(v, lane_up<4>(v));
+    if constexpr (L > 2) v = fmax(v, lane_up<2>(v));
+    if constexpr (L > 1) v = fmax(v, lane_up<1>(v));
     return v;
 }
 
-__device__ __forceinline__ double wave_max(double v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-    return v;
-}
+// in lane 0
+__device__ __forceinline__ double wave_sum(double v) { return group_sum<64>(v); }
+__device__ __forceinline__ double wave_max(double v) { return group_max<64>(v); }
 
 // Workgroup reduction of NQ values (sum, or max where is_max bit q is set);
 // thread 0 receives the results.  Uses kBlock/64 LDS slots per quantity.
@@ -96,8 +130,8 @@ __device__ __forceinline__ int xcd_block(int bid, int nblk)
 // below end, accumulated in that order.  Four terms' index, value and
 // gathered loads are issued before the first of them is accumulated, so a
 // lane waits for one round of loads per four terms instead of per term.
-template <int L, typename ACC, typename VM, typename VX>
-__device__ __forceinline__ ACC lane_dot(int beg, int end, int lane, const int *__restrict__ idx,
+template <int L, typename ACC, typename I, typename VM, typename VX>
+__device__ __forceinline__ ACC lane_dot(int beg, int end, int lane, const I *__restrict__ idx,
                                         const VM *__restrict__ val, const VX *__restrict__ x)
 {
     ACC acc = 0;

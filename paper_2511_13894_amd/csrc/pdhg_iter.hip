@@ -32,10 +32,11 @@ __global__ __launch_bounds__(kBlock) void k_primal(int n, const int *__restrict_
     // after the product, measured no faster)
     const double aj = xa[j], xj = iterate_value<V>(x[j], aj), cj = ch[j], lo = (double)lh[j], hi = (double)uh[j];
     if (st->done) return;
+    const StepScalars sc = step_scalars(st, i);
     double acc = lane_dot<L, double>(tp[j], tp[j + 1], lane, ti, atv, y);
     acc = group_sum<L>(acc);
     if (lane != 0) return;
-    primal_update<V>(j, acc, xj, cj, lo, hi, aj, x, xbar, xp, st, i, store_cand);
+    primal_update<V>(j, acc, xj, cj, lo, hi, aj, x, xbar, xp, sc, store_cand);
 }
 
 // Dual half on rows [row0, row1), one row of A per group of L lanes, for the
@@ -55,10 +56,11 @@ __device__ __forceinline__ void dual_rows(int row0, int row1, int lb, const int 
     const double yr = y[r], br = bh[r], ar = ya[r]; // epilogue operands (see k_primal)
     const int8_t sn = sense[r];
     if (st->done) return;
+    const StepScalars sc = step_scalars(st, i);
     double acc = lane_dot<L, double>(rp[r], rp[r + 1], lane, ci, av, xbar);
     acc = group_sum<L>(acc);
     if (lane != 0) return;
-    dual_update(r, acc, yr, br, ar, sn, y, yp, st, i, store_cand);
+    dual_update(r, acc, yr, br, ar, sn, y, yp, sc, store_cand);
 }
 
 // Dual half, one row of A per group of L lanes:  h = Ahat xbar.
@@ -170,8 +172,7 @@ __global__ __launch_bounds__(kBlock) void k_row_adjacent(int m, const int *__res
     const int beg = rp[w], end = rp[w + 1];
     int c = 0;
     for (int e = beg + lane; e + 1 < end; e += 64) c += ci[e + 1] == ci[e] + 1 ? 1 : 0;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
+    c = group_sum<64>(c);
     if (lane == 0) adj[w] = c;
 }
 
@@ -345,8 +346,9 @@ __global__ __launch_bounds__(kBlock) void k_primal_rowblock(int n, const int *__
         lo = (double)lh[j];
         hi = (double)uh[j];
     }
+    const StepScalars sc = step_scalars(st, i);
     const double g = row_block_sum<V, double>(tp[j], tp[j + 1], ti, atv, y);
-    if (threadIdx.x == 0) primal_update<V>(j, g, xj, cj, lo, hi, aj, x, xbar, xp, st, i, store_cand);
+    if (threadIdx.x == 0) primal_update<V>(j, g, xj, cj, lo, hi, aj, x, xbar, xp, sc, store_cand);
 }
 
 template <typename V>
@@ -367,8 +369,9 @@ __global__ __launch_bounds__(kBlock) void k_dual_rowblock(int m, const int *__re
         ar = ya[r];
         sn = sense[r];
     }
+    const StepScalars sc = step_scalars(st, i);
     const double h = row_block_sum<V, V>(rp[r], rp[r + 1], ci, av, xbar);
-    if (threadIdx.x == 0) dual_update(r, h, yr, br, ar, sn, y, yp, st, i, store_cand);
+    if (threadIdx.x == 0) dual_update(r, h, yr, br, ar, sn, y, yp, sc, store_cand);
 }
 
 template <typename V, int T, int NT>
@@ -396,9 +399,10 @@ __global__ __launch_bounds__(NT) void k_primal_tiled(int n, const int *__restric
     const double aj = xa[jc], xj = iterate_value<V>(x[jc], aj), cj = ch[jc], lo = (double)lh[jc],
                  hi = (double)uh[jc];
     if (st->done) return;
+    const StepScalars sc = step_scalars(st, i);
     tile_row_sums<V, double, T, NT>(r0, rows, tp, ti, atv, y, s_ptr, s_prod, s_sum);
     if (!mine) return;
-    primal_update<V>(j, s_sum[tid], xj, cj, lo, hi, aj, x, xbar, xp, st, i, store_cand);
+    primal_update<V>(j, s_sum[tid], xj, cj, lo, hi, aj, x, xbar, xp, sc, store_cand);
 }
 
 template <typename V, int T, int NT>
@@ -421,9 +425,10 @@ __global__ __launch_bounds__(NT) void k_dual_tiled(int m, const int *__restrict_
     const double yr = y[rc], br = bh[rc], ar = ya[rc];
     const int8_t sn = sense[rc];
     if (st->done) return;
+    const StepScalars sc = step_scalars(st, i);
     tile_row_sums<V, V, T, NT>(r0, rows, rp, ci, av, xbar, s_ptr, s_prod, s_sum);
     if (!mine) return;
-    dual_update(r, s_sum[tid], yr, br, ar, sn, y, yp, st, i, store_cand);
+    dual_update(r, s_sum[tid], yr, br, ar, sn, y, yp, sc, store_cand);
 }
 
 // Primal half when every column of A has the same D <= 3 entries (every
@@ -452,6 +457,7 @@ __global__ __launch_bounds__(kBlock) void k_primal_udeg(int n, const int *__rest
     }
     const double aj = xa[j], xj = iterate_value<V>(x[j], aj), cj = ch[j], lo = (double)lh[j], hi = (double)uh[j];
     if (st->done) return;
+    const StepScalars sc = step_scalars(st, i);
     double g[D];
 #pragma unroll
     for (int d = 0; d < D; d++) g[d] = y[id[d]];
@@ -462,7 +468,7 @@ __global__ __launch_bounds__(kBlock) void k_primal_udeg(int n, const int *__rest
 #pragma unroll
         for (int d = 0; d < D; d++) acc = acc + v[d] * g[d];
     }
-    primal_update<V>(j, acc, xj, cj, lo, hi, aj, x, xbar, xp, st, i, store_cand);
+    primal_update<V>(j, acc, xj, cj, lo, hi, aj, x, xbar, xp, sc, store_cand);
 }
 
 template <typename V>

@@ -12,13 +12,27 @@
 
 namespace pdhg {
 
-// Halpern weights for iteration number k (0-based since the last restart).
-__device__ __forceinline__ void halpern_weights(const DevState *st, int i, double &w, double &wa, double &g)
+// An iteration's scalars: step sizes, reflection and the Halpern weights of
+// iteration number k = k0 + i (0-based since the last restart).  The kernels
+// form them before the row products, so the two divisions run while the
+// products' loads are on their way instead of after them.
+struct StepScalars {
+    double tau, sigma, gamma;
+    double w, wa; // (k + 1) / (k + 2), 1 / (k + 2)
+    int halpern;
+};
+
+__device__ __forceinline__ StepScalars step_scalars(const DevState *__restrict__ st, int i)
 {
     const double k = (double)(st->k0 + i);
-    w = (k + 1.0) / (k + 2.0);
-    wa = 1.0 / (k + 2.0);
-    g = st->gamma;
+    return StepScalars{st->tau, st->sigma, st->gamma, (k + 1.0) / (k + 2.0), 1.0 / (k + 2.0), st->halpern};
+}
+
+// w ((1+gamma) v - gamma old) + wa anchor, with its fused steps spelled out:
+// every kernel that makes this update must round it alike.
+__device__ __forceinline__ double halpern_average(double v, double old, double anchor, const StepScalars &q)
+{
+    return __builtin_fma(__builtin_fma(1.0 + q.gamma, v, -(q.gamma * old)), q.w, q.wa * anchor);
 }
 
 // Storage.  Float64 mode: every vector is double.  Mixed mode (V = float):
@@ -37,35 +51,44 @@ __device__ __forceinline__ void halpern_weights(const DevState *st, int i, doubl
 // rounding).  All arithmetic — products, sums, projections, Halpern averages —
 // is double in registers; only the stores round to V.
 
-// Primal half, one row of the transpose (= one column j of A) per group of L
-// lanes:  g = Ahat' y;  x+ = clamp(x - tau (chat - g),
-// lhat, uhat);  xbar = 2 x+ - x;  x <- w ((1+gamma) x+ - gamma x) + wa x_a.
-// xj is the iterate itself (mixed: x_a + stored difference), aj the anchor.
-// At the last iteration before a check the candidate x+ is stored as well.
+// Primal half of column j from its product g = (Ahat' y)_j:  x+ = clamp(x -
+// tau (chat - g), lhat, uhat);  xbar = 2 x+ - x;  x <- w ((1+gamma) x+ - gamma
+// x) + wa x_a.  xj is the iterate itself (mixed: x_a + stored difference), aj
+// the anchor; x and xbar come back as they are stored.
 template <typename V>
-__device__ __forceinline__ void primal_update(int64_t j, double g, double xj, double cj, double lo, double hi,
-                                              double aj, V *__restrict__ x, V *__restrict__ xbar,
-                                              double *__restrict__ xp, const DevState *__restrict__ st, int i,
-                                              int store_cand)
+struct PrimalStep {
+    double cand; // x+
+    V x, xbar;
+};
+
+template <typename V>
+__device__ __forceinline__ PrimalStep<V> primal_step(double g, double xj, double cj, double lo, double hi, double aj,
+                                                     const StepScalars &q)
 {
     constexpr bool delta = sizeof(V) == sizeof(float);
-    double xn = xj - st->tau * (cj - g);
+    double xn = __builtin_fma(-(cj - g), q.tau, xj);
     xn = xn < lo ? lo : xn;
     xn = xn > hi ? hi : xn;
     const double xb = 2.0 * xn - xj;
+    const double xnew = q.halpern ? halpern_average(xn, xj, aj, q) : xn;
+    return PrimalStep<V>{xn, (V)(delta ? xnew - aj : xnew), (V)(delta ? xb - aj : xb)};
+}
+
+// The primal half's epilogue of column j; at the last iteration before a
+// check the candidate x+ is stored as well.
+template <typename V>
+__device__ __forceinline__ void primal_update(int64_t j, double g, double xj, double cj, double lo, double hi,
+                                              double aj, V *__restrict__ x, V *__restrict__ xbar,
+                                              double *__restrict__ xp, const StepScalars &q, int store_cand)
+{
+    const PrimalStep<V> p = primal_step<V>(g, xj, cj, lo, hi, aj, q);
     // x and xbar go out as non-temporal stores: only the next launch reads
     // them (the dual half xbar, the next primal half x), from beyond this
     // XCD's L2 in any case, and lines left dirty in the L2 are written back
     // before the launch can end (c2 push: 5.8 -> 5.4 us per launch)
-    __builtin_nontemporal_store((V)(delta ? xb - aj : xb), &xbar[j]);
-    if (store_cand) xp[j] = xn;
-    double xnew = xn;
-    if (st->halpern) {
-        double w, wa, gm;
-        halpern_weights(st, i, w, wa, gm);
-        xnew = w * ((1.0 + gm) * xn - gm * xj) + wa * aj;
-    }
-    __builtin_nontemporal_store((V)(delta ? xnew - aj : xnew), &x[j]);
+    __builtin_nontemporal_store(p.xbar, &xbar[j]);
+    if (store_cand) xp[j] = p.cand;
+    __builtin_nontemporal_store(p.x, &x[j]);
 }
 
 // set the iterate of column j to v (mixed mode: as the anchor, difference 0;
@@ -89,23 +112,26 @@ __device__ __forceinline__ double iterate_value(V stored, double anchor)
     return sizeof(V) == sizeof(float) ? anchor + (double)stored : (double)stored;
 }
 
-// Dual half:  y+ = proj_Y(y + sigma (bhat - h));  y <- w ((1+gamma) y+ - gamma y) + wa y_anchor.
-__device__ __forceinline__ void dual_update(int64_t r, double h, double yr, double br, double ar, int8_t sn,
-                                            double *__restrict__ y, double *__restrict__ yp,
-                                            const DevState *__restrict__ st, int i, int store_cand)
+// Dual half of row r from its product h = (Ahat xbar)_r:  y+ = proj_Y(y +
+// sigma (bhat - h));  y <- w ((1+gamma) y+ - gamma y) + wa y_anchor.
+__device__ __forceinline__ double dual_step(double h, double yr, double br, double ar, int8_t sn, const StepScalars &q,
+                                            double &cand)
 {
-    double yn = yr + st->sigma * (br - h);
+    double yn = __builtin_fma(br - h, q.sigma, yr);
     if (sn == '<') yn = yn < 0.0 ? yn : 0.0;
     else if (sn == '>') yn = yn > 0.0 ? yn : 0.0;
     else if (sn == 'N') yn = 0.0; // a row the dual push drops: y_i = 0
-    if (store_cand) yp[r] = yn;
-    double ynew = yn;
-    if (st->halpern) {
-        double w, wa, gm;
-        halpern_weights(st, i, w, wa, gm);
-        ynew = w * ((1.0 + gm) * yn - gm * yr) + wa * ar;
-    }
-    y[r] = ynew;
+    cand = yn;
+    return q.halpern ? halpern_average(yn, yr, ar, q) : yn;
+}
+
+__device__ __forceinline__ void dual_update(int64_t r, double h, double yr, double br, double ar, int8_t sn,
+                                            double *__restrict__ y, double *__restrict__ yp, const StepScalars &q,
+                                            int store_cand)
+{
+    double cand;
+    y[r] = dual_step(h, yr, br, ar, sn, q, cand);
+    if (store_cand) yp[r] = cand;
 }
 
 // ------------------------------------------------- LDS-tiled short rows ---

@@ -172,6 +172,15 @@ __global__ __launch_bounds__(kBlock) void k_mlp_forward(const FT *__restrict__ F
 // (W2^T from a transposed copy): 18.6 -> 13.1 us.
 __device__ __forceinline__ float softplus(float x) { return x > 0.0f ? x + log1pf(expf(-x)) : log1pf(expf(x)); }
 
+// sum over each row of 16 lanes, neighbours first, in the row's lowest lane
+__device__ __forceinline__ float pair_sum16(float v)
+{
+    v += lane_up<1>(v);
+    v += lane_up<2>(v);
+    v += lane_up<4>(v);
+    return v + lane_up<8>(v);
+}
+
 constexpr int kGradTiles = 2; // tiles of 16 samples per wave
 
 __global__ __launch_bounds__(64) void k_mlp_grad(const short *__restrict__ F, const float *__restrict__ Y,
@@ -348,23 +357,21 @@ __global__ __launch_bounds__(64) void k_mlp_grad(const short *__restrict__ F, co
 #pragma unroll
             for (int nb = 0; nb < 4; nb++) out[OFF_W2 + h * 64 + 16 * nb + lr] = gw2[mb][nb][r];
             float s1 = gb1[mb][r], s2 = gb2[mb][r], s3 = gw3[mb][r];
-#pragma unroll
-            for (int off = 1; off < 16; off <<= 1) {
-                s1 += __shfl_xor(s1, off, 64);
-                s2 += __shfl_xor(s2, off, 64);
-                s3 += __shfl_xor(s3, off, 64);
-            }
+            s1 = pair_sum16(s1);
+            s2 = pair_sum16(s2);
+            s3 = pair_sum16(s3);
             if (lr == 0) {
                 out[OFF_B1 + h] = s1;
                 out[OFF_B2 + h] = s2;
                 out[OFF_W3 + h] = s3;
             }
         }
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        gb3 += __shfl_xor(gb3, off, 64);
-        loss += __shfl_xor(loss, off, 64);
-    }
+    gb3 = pair_sum16(gb3);
+    loss = pair_sum16(loss);
+    gb3 += lane_up<16>(gb3);
+    loss += lane_up<16>(loss);
+    gb3 += lane_up<32>(gb3);
+    loss += lane_up<32>(loss);
     if (lane == 0) {
         out[OFF_B3] = gb3;
         lossp[gw] = loss;

@@ -82,7 +82,8 @@ __global__ __launch_bounds__(kBlock) void k_sell_dual_finish(int m, const int *_
     const int s = r / kSellC, lane = r % kSellC;
     double h = 0.0;
     for (int w = wi_start[s]; w < wi_start[s + 1]; w++) h += part[(size_t)w * kSellC + lane];
-    dual_update(r, h, y[r], bh[r], ya[r], sense[r], y, yp, st, i, store_cand);
+    const StepScalars sc = step_scalars(st, i);
+    dual_update(r, h, y[r], bh[r], ya[r], sense[r], y, yp, sc, store_cand);
 }
 
 __global__ __launch_bounds__(kBlock) void k_sell_product_finish(int m, const int *__restrict__ wi_start,

@@ -423,11 +423,7 @@ __global__ __launch_bounds__(kBlock) void k_row_norm(int rows, const int *__rest
         if (MODE == 0) acc = fmax(acc, a);
         else acc += (p == 1.0) ? a : pow(a, p);
     }
-#pragma unroll
-    for (int off = L / 2; off > 0; off >>= 1) {
-        double o = __shfl_xor(acc, off, L);
-        acc = (MODE == 0) ? fmax(acc, o) : acc + o;
-    }
+    acc = MODE == 0 ? group_max<L>(acc) : group_sum<L>(acc);
     if (lane == 0) out[row] = acc > 0.0 ? sqrt(acc) : 1.0;
 }
 
