@@ -71,7 +71,7 @@ def make_lp(cfg):
 # features play no part in it).  A counter summary counts only while this
 # hash is unchanged.
 SOURCE_FILES = ("pdhg_iter.hip", "pdhg_kernels.hpp", "pdhg_device.hpp", "pdhg_internal.hpp", "pdhg_setup.hip",
-                "pdhg_compact.hip", "pdhg_sell.hip", "pdhg_batch.hip", "pdhg_capi.cpp", "../lpgen.py")
+                "pdhg_compact.hip", "pdhg_resident.hip", "pdhg_sell.hip", "pdhg_batch.hip", "pdhg_capi.cpp", "../lpgen.py")
 
 
 def kernel_source_hash(files=SOURCE_FILES):

@@ -424,6 +424,7 @@ static int build_solver(int m, int n, int nz, const pdhg_params &p, const ModelS
         s->nnz = nz;
         s->p = p;
         s->fp32 = p.precision == PDHG_FP32_MIXED;
+        s->lone = single;
         if (p.timing)
             for (hipEvent_t &e : s->ev) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableSystemFence));
         if (p.stream) s->stream = (hipStream_t)p.stream;
@@ -545,6 +546,7 @@ static int build_solver(int m, int n, int nz, const pdhg_params &p, const ModelS
         if (s->kern_a == kRowSegs || (single && p.autotune)) HIPCHK(plan_row_segments(s));
         if (s->kern_a == kSell) HIPCHK(sell_build(s, rp_host));
         if (single) {
+            HIPCHK(resident_plan(s));
             HIPCHK(power_iteration(s));
             HIPCHK(init_norms(s));
             HIPCHK(init_iteration(s));

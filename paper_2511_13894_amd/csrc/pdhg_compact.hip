@@ -351,6 +351,7 @@ hipError_t begin_impl(pdhg_solver *s)
     c.chc0 = s->chc;
     c.bhc0 = s->bhc;
     c.segs0 = s->segs;
+    c.res0 = s->res;
     s->n = nf;
     s->nnz = nnz_f;
     s->red_blocks_n = grid_for(nf, kBlock, kMaxRedBlocks);
@@ -390,7 +391,8 @@ hipError_t begin_impl(pdhg_solver *s)
         s->graph_mode = -1;
     }
     if (s->kern_a == kRowSegs && (e = plan_row_segments(s)) != hipSuccess) return e; // of the compact rows
-    return detect_uniform_columns(s); // of the compact model (on failure the caller restores the full one)
+    if ((e = detect_uniform_columns(s)) != hipSuccess) return e; // of the compact model (on failure the caller restores the full one)
+    return resident_plan(s);
 }
 
 template <typename V>
@@ -429,6 +431,7 @@ hipError_t end_impl(pdhg_solver *s, bool scatter)
     s->chc = c.chc0;
     s->bhc = c.bhc0;
     s->segs = c.segs0;
+    s->res = c.res0;
     s->defect_stale = true;
     if (c.lfix0) {
         s->lfix = c.lfix0;

@@ -100,6 +100,7 @@ struct pdhg_solver {
     pdhg_params p{};
     hipStream_t stream = nullptr;
     bool own_stream = false;
+    bool lone = false; // one LP of its own, not the model of a batch
     bool fp32 = false;
 
     // original model, float64, row-compressed A and its explicit transpose
@@ -154,6 +155,14 @@ struct pdhg_solver {
     int udeg_at = 0;               // every column holds this many entries (1..3), else 0
     int kern_at = 1, kern_a = 1;   // iteration kernels: > 0 lane-group width, < 0 LDS tile of -k rows
     pdhg::RowSegs segs;            // the dual half's row segments (kern_a == kRowSegs)
+    // a small LP's iterations in one workgroup: kernel variant (0: none), the
+    // longest column, and the dual half's rounds of rows (first, past the last,
+    // log2 threads per row, accumulators and entries per thread)
+    struct Resident {
+        int variant = 0, ep = 0, rounds = 0;
+        bool fma = false;
+        int row0[2] = {}, row1[2] = {}, hs[2] = {}, acc[2] = {}, slots[2] = {};
+    } res;
     int64_t t_host = 0;      // iterations of the current phase (mirror of st->t)
     int64_t power_steps = 0; // power-iteration steps taken at create
     int64_t next_check = 0;  // phase iteration count of the next check
@@ -211,6 +220,7 @@ struct pdhg_solver {
         void *aerr0 = nullptr, *aerr_t0 = nullptr;
         double *chc0 = nullptr, *bhc0 = nullptr;
         pdhg::RowSegs segs0;
+        Resident res0;
     } pc;
 
     // live kernel timing: events around one primal and one dual launch per cycle
@@ -344,6 +354,12 @@ hipError_t sell_build(pdhg_solver *s, const std::vector<int> &rp_host);
 void sell_dual(pdhg_solver *s, int i, int store, hipEvent_t e0, hipEvent_t e1);
 void sell_product(pdhg_solver *s, const double *vec, double *out);
 void sell_product(pdhg_solver *s, const float *vec, double *out);
+
+// the iterations of a small LP in one workgroup (pdhg_resident.hip); the plan
+// follows the current model and its kernel choice (variant 0: launched kernels)
+constexpr int kResMaxNnz = 32768; // more entries than the largest variant holds
+hipError_t resident_plan(pdhg_solver *s);
+hipError_t resident_iterations(pdhg_solver *s, int count, bool store_candidate);
 
 // iteration, checks, push and reports (pdhg_iter.hip)
 hipError_t init_iteration(pdhg_solver *s);

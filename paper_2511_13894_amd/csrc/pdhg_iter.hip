@@ -890,7 +890,12 @@ hipError_t launch_advance(pdhg_solver *s, int len)
 hipError_t launch_iterations(pdhg_solver *s, int count, bool check_at_end, int mode, bool timed_launch)
 {
     const int timed = (timed_launch && count >= 2) ? count / 2 : -1; // one sampled iteration
-    for (int i = 0; i < count; i++) {
+    const bool resident = timed < 0 && s->res.variant > 0; // a sampled segment launches every half
+    if (resident) {
+        hipError_t e = resident_iterations(s, count, check_at_end);
+        if (e != hipSuccess) return e;
+    }
+    for (int i = 0; i < count && !resident; i++) {
         const int store = (check_at_end && i == count - 1) ? 1 : 0;
         hipEvent_t *ev = i == timed ? s->ev : nullptr;
         if (s->fp32) launch_primal<float>(s, i, store, ev ? ev[0] : nullptr, ev ? ev[1] : nullptr);
