@@ -460,7 +460,7 @@ __global__ __launch_bounds__(kBlock) void kb_power_finish(const int *__restrict_
         const double rho = q[0], ww = q[1], lam = sqrt(ww);
         ps[lp] = lam;
         ps[2 * count + lp] += 1.0;
-        if (!(lam > 0.0) || sqrt(fmax(ww - rho * rho, 0.0)) <= tol * rho) ps[count + lp] = 1.0;
+        if (power_stops(rho, ww, lam, tol)) ps[count + lp] = 1.0;
     }
 }
 

@@ -130,7 +130,14 @@ int run_phase(pdhg_solver *s, int64_t iters, int mode, double t0)
             // with timing on, the first segment of every batch runs eagerly with
             // events around one primal and one dual launch; the rest replay
             const bool timed = s->p.timing && enq == 0 && len >= 2;
-            if (check && len == K && s->p.use_graph && !timed) {
+            int64_t cycles = check && !timed ? resident_cycles_max(s, mode, len) : 0;
+            if (cycles > 0) { // a small LP: several cycles in one launch, up to the target
+                cycles = std::min<int64_t>(cycles, 1 + (left - len) / K);
+                HIPCHK(resident_cycles(s, len, (int)cycles, mode));
+                s->t_host += (cycles - 1) * K;
+                s->next_check += (cycles - 1) * K;
+                enq = depth; // then look at the state
+            } else if (check && len == K && s->p.use_graph && !timed) {
                 HIPCHK(capture_cycle(s, K, mode));
                 HIPCHK(hipGraphLaunch(s->graph_exec, s->stream));
             } else {

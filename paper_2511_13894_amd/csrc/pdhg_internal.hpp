@@ -360,6 +360,13 @@ void sell_product(pdhg_solver *s, const float *vec, double *out);
 constexpr int kResMaxNnz = 32768; // more entries than the largest variant holds
 hipError_t resident_plan(pdhg_solver *s);
 hipError_t resident_iterations(pdhg_solver *s, int count, bool store_candidate);
+// whole cycles in one launch, a first one of `first` iterations and later ones
+// of check_every, each with its check of `mode`; at most resident_cycles_max
+// of them (0: this handle or phase takes launched checks)
+int resident_cycles_max(const pdhg_solver *s, int mode, int first);
+hipError_t resident_cycles(pdhg_solver *s, int first, int cycles, int mode);
+// the power iteration in one launch (pw as in power_iteration)
+hipError_t resident_power(pdhg_solver *s, double *pw);
 
 // iteration, checks, push and reports (pdhg_iter.hip)
 hipError_t init_iteration(pdhg_solver *s);

@@ -356,6 +356,13 @@ __device__ __forceinline__ void check_model(bool orig, int64_t j, const double *
     }
 }
 
+// The power iteration's stop: with v of unit length, rho = u'u and w'w, the
+// eigen-residual sqrt(w'w - rho^2) against tol rho (or w = 0).
+__device__ __forceinline__ bool power_stops(double rho, double ww, double lam, double tol)
+{
+    return !(lam > 0.0) || sqrt(fmax(__builtin_fma(-rho, rho, ww), 0.0)) <= tol * rho;
+}
+
 // splitmix64 (Steele, Lea and Flood 2014)
 __device__ __forceinline__ uint64_t splitmix64(uint64_t x)
 {

@@ -616,7 +616,7 @@ __global__ __launch_bounds__(kBlock) void k_power_finish(int gm, int gn, const d
         const double rho = v[0], ww = v[1], lam = sqrt(ww);
         pw[0] = lam;
         pw[2] += 1.0;
-        if (!(lam > 0.0) || sqrt(fmax(ww - rho * rho, 0.0)) <= tol * rho) pw[1] = 1.0;
+        if (power_stops(rho, ww, lam, tol)) pw[1] = 1.0;
     }
 }
 
@@ -649,7 +649,9 @@ hipError_t power_iteration(pdhg_solver *s)
     if ((e = hipMalloc(&pw, 4 * sizeof(double))) != hipSuccess) return e;
     hipMemsetAsync(pw, 0, 4 * sizeof(double), st);
     const int gm = grid_for(m, kBlock, kMaxRedBlocks), gn = grid_for(n, kBlock, kMaxRedBlocks);
-    if (n > 0) { // start: v = (1 + U) / ||1 + U||, the norm kept in pw[3]
+    const bool resident = s->res.variant > 0; // a small LP's steps in one launch
+    if (resident && (e = resident_power(s, pw)) != hipSuccess) return e;
+    if (n > 0 && !resident) { // start: v = (1 + U) / ||1 + U||, the norm kept in pw[3]
         const int gv = grid_for(n, kBlock, 1 << 30);
         hipLaunchKernelGGL(k_power_start, dim3(gv), dim3(kBlock), 0, st, (int64_t)n, v);
         hipLaunchKernelGGL(k_sumsq_partials, dim3(gn), dim3(kBlock), 0, st, n, v, s->partials);
@@ -658,7 +660,7 @@ hipError_t power_iteration(pdhg_solver *s)
     }
     double pw_host[4] = {0.0, 0.0, 0.0, 0.0};
     constexpr int kPowerBatch = 32; // steps launched between reads of the done flag
-    for (int it = 0; it < s->p.power_iters && n > 0 && m > 0; it += kPowerBatch) {
+    for (int it = 0; it < s->p.power_iters && n > 0 && m > 0 && !resident; it += kPowerBatch) {
         const int len = std::min(kPowerBatch, s->p.power_iters - it);
         for (int k = 0; k < len; k++) {
             (void)solver_product(s, false, v, u);
@@ -672,6 +674,8 @@ hipError_t power_iteration(pdhg_solver *s)
         if ((e = hipStreamSynchronize(st)) != hipSuccess) break;
         if (pw_host[1] != 0.0) break;
     }
+    if (resident && (e = hipMemcpyAsync(pw_host, pw, 4 * sizeof(double), hipMemcpyDeviceToHost, st)) == hipSuccess)
+        e = hipStreamSynchronize(st);
     s->power_steps = (int64_t)pw_host[2];
     if (e == hipSuccess) {
         hipLaunchKernelGGL(k_set_step, dim3(1), dim3(1), 0, st, s->st, pw, s->p.eta_safety);

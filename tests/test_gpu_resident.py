@@ -4,7 +4,8 @@ library's own takes the launched path, and both must give the same bits, in
 iterates, solve and pushes.  Sizes at the edges of its rules: one row or
 column, rows of one and of many lane groups, tiles longer than a chunk of
 entries, more than 4,096 columns (operands from memory), matrices just inside
-and outside the LDS, and iteration counts that are not a multiple of a check."""
+and outside the LDS, and iteration counts that are not a multiple of a check.
+The power iteration and the checks run in the workgroup too."""
 import numpy as np
 import pytest
 
@@ -53,6 +54,8 @@ def test_resident_equals_launched(name, precision):
     print(f"[resident] {name} {precision}: m={lp.m} n={lp.n} nnz={lp.nnz}", flush=True)
     r = pdhg.Solver(lp, precision=precision)
     k = pdhg.Solver(lp, precision=precision, **_own_choice(lp, precision))
+    a, b = r.get_scaling(), k.get_scaling()
+    assert (a["eta"], a["sigma_est"], a["power_steps"]) == (b["eta"], b["sigma_est"], b["power_steps"])
     for count in (1, 5, 64, 130):
         a, b = r.iterate(count), k.iterate(count)
         assert (a.status, a.iters, a.restarts) == (b.status, b.iters, b.restarts)
@@ -80,3 +83,33 @@ def test_resident_equals_launched_options(kw):
     a, b = r.solve(), k.solve()
     assert (a.status, a.iters, a.restarts) == (b.status, b.iters, b.restarts)
     _same(r.get_solution(), k.get_solution())
+
+
+def test_resident_solve_after_a_restored_state_and_a_new_start():
+    lp = LPS["c0"]
+    r, k = pdhg.Solver(lp, precision="fp32"), pdhg.Solver(lp, precision="fp32", **_own_choice(lp, "fp32"))
+    r.iterate(100)  # between two checks
+    k.set_state(r.get_state())
+    a, b = r.solve(), k.solve()
+    assert (a.status, a.iters, a.restarts) == (b.status, b.iters, b.restarts)
+    _same(r.get_solution(), k.get_solution())
+    x, y = np.full(lp.n, 0.1), np.full(lp.m, -0.2)
+    for s in (r, k):
+        s.set_start(x, y)
+    a, b = r.solve(), k.solve()
+    assert (a.status, a.iters, a.restarts) == (b.status, b.iters, b.restarts)
+    _same(r.get_solution(), k.get_solution())
+
+
+def test_resident_learned_push_and_history():
+    lp = LPS["c0"]
+    logits = np.random.default_rng(1).standard_normal(lp.n) * 3
+    got = []
+    for kw in ({}, _own_choice(lp, "fp64")):
+        s = pdhg.Solver(lp, record_history=1, **kw)
+        a = s.solve()
+        f = s.features(5)
+        b = s.corner_push_logits(logits, 0.9, 5)
+        got.append((a.iters, a.restarts, b.status, b.iters, b.n_learned_fix, b.n_learned_undo, f, *s.get_solution()))
+    for u, v in zip(*got):
+        np.testing.assert_array_equal(u, v)
