@@ -48,7 +48,7 @@ __global__ __launch_bounds__(NT) void kb_primal(const int4 *__restrict__ tiles, 
         hi = (double)uh[j];
     }
     const StepScalars sc = step_scalars(st, i);
-    tile_row_sums<V, double, T, NT>(r0, rows, tp, ti, atv, y, s_ptr, s_prod, s_sum);
+    tile_row_sums<V, double, T, NT>(tile_range(tp, r0, rows), r0, rows, tp, ti, atv, y, s_ptr, s_prod, s_sum);
     if (!mine) return;
     primal_update<V>(j, s_sum[tid], xj, cj, lo, hi, aj, x, xbar, xp, sc, store_cand);
 }
@@ -80,7 +80,7 @@ __global__ __launch_bounds__(NT) void kb_dual(const int4 *__restrict__ tiles, co
         sn = sense[r];
     }
     const StepScalars sc = step_scalars(st, i);
-    tile_row_sums<V, V, T, NT>(r0, rows, rp, ci, av, xbar, s_ptr, s_prod, s_sum);
+    tile_row_sums<V, V, T, NT>(tile_range(rp, r0, rows), r0, rows, rp, ci, av, xbar, s_ptr, s_prod, s_sum);
     if (!mine) return;
     dual_update(r, s_sum[tid], yr, br, ar, sn, y, yp, sc, store_cand);
 }
@@ -315,7 +315,7 @@ __global__ __launch_bounds__(NT) void kb_spmv(const int4 *__restrict__ tiles, co
     __shared__ double s_sum[T];
     const int4 tl = tiles[xcd_range_block(blockIdx.x, gridDim.x)];
     if (sts ? sts[tl.x].done != 0 : skip[tl.x] != 0.0) return; // uniform over the workgroup
-    tile_row_sums<VM, VV, T, NT>(tl.y, tl.z, ptr, idx, val, vec, s_ptr, s_prod, s_sum);
+    tile_row_sums<VM, VV, T, NT>(tile_range(ptr, tl.y, tl.z), tl.y, tl.z, ptr, idx, val, vec, s_ptr, s_prod, s_sum);
     if ((int)threadIdx.x < tl.z) out[tl.y + threadIdx.x] = s_sum[threadIdx.x];
 }
 

@@ -224,7 +224,7 @@ __global__ __launch_bounds__(NT) void k_spmv_tiled(int rows_total, const int *__
     __shared__ double s_sum[T];
     const int r0 = xcd_block(blockIdx.x, gridDim.x) * T;
     const int rows = rows_total - r0 < T ? rows_total - r0 : T;
-    tile_row_sums<VM, VV, T, NT>(r0, rows, ptr, idx, val, vec, s_ptr, s_prod, s_sum);
+    tile_row_sums<VM, VV, T, NT>(tile_range(ptr, r0, rows), r0, rows, ptr, idx, val, vec, s_ptr, s_prod, s_sum);
     if ((int)threadIdx.x < rows) out[r0 + threadIdx.x] = s_sum[threadIdx.x];
 }
 
@@ -398,9 +398,11 @@ __global__ __launch_bounds__(NT) void k_primal_tiled(int n, const int *__restric
     const int jc = mine ? j : r0;
     const double aj = xa[jc], xj = iterate_value<V>(x[jc], aj), cj = ch[jc], lo = (double)lh[jc],
                  hi = (double)uh[jc];
-    if (st->done) return;
+    const int done = st->done;
+    const TileRange range = tile_range(tp, r0, rows);
+    if (done) return;
     const StepScalars sc = step_scalars(st, i);
-    tile_row_sums<V, double, T, NT>(r0, rows, tp, ti, atv, y, s_ptr, s_prod, s_sum);
+    tile_row_sums<V, double, T, NT>(range, r0, rows, tp, ti, atv, y, s_ptr, s_prod, s_sum);
     if (!mine) return;
     primal_update<V>(j, s_sum[tid], xj, cj, lo, hi, aj, x, xbar, xp, sc, store_cand);
 }
@@ -424,9 +426,11 @@ __global__ __launch_bounds__(NT) void k_dual_tiled(int m, const int *__restrict_
     const int rc = mine ? r : r0; // as in k_primal_tiled: unconditional epilogue loads
     const double yr = y[rc], br = bh[rc], ar = ya[rc];
     const int8_t sn = sense[rc];
-    if (st->done) return;
+    const int done = st->done;
+    const TileRange range = tile_range(rp, r0, rows);
+    if (done) return;
     const StepScalars sc = step_scalars(st, i);
-    tile_row_sums<V, V, T, NT>(r0, rows, rp, ci, av, xbar, s_ptr, s_prod, s_sum);
+    tile_row_sums<V, V, T, NT>(range, r0, rows, rp, ci, av, xbar, s_ptr, s_prod, s_sum);
     if (!mine) return;
     dual_update(r, s_sum[tid], yr, br, ar, sn, y, yp, sc, store_cand);
 }
