@@ -83,14 +83,9 @@ const double *cur_z(const pdhg_solver *s) { return s->dual_pushed ? s->zpush : s
 void free_all(pdhg_solver *s)
 {
     (void)push_compact_end(s, false);
-    void *ptrs[] = {s->rp,   s->ci, s->av,  s->tp,   s->ti,     s->tperm, s->atv,  s->b,   s->c,       s->l,
-                    s->u,    s->sense0, s->dr, s->dc, s->ahat, s->ahat_t, s->x,   s->y,     s->xa,   s->ya,
-                    s->xbar, s->xp, s->yp,  s->ch,   s->bh,     s->lh,    s->uh,   s->xs,  s->ys,      s->sense,
-                    s->ax,   s->aty, s->xu, s->yu,   s->zsol,   s->xpush, s->partials, s->redout, s->st,
-                    s->hx,   s->hz,  s->feat_raw, s->feat_b, s->logits, s->lfix, s->lcount, s->sell_idx,
+    void *ptrs[] = {s->slab,     s->feat_raw, s->feat_b,   s->logits,  s->lfix,          s->lcount,  s->sell_idx,
                     s->sell_val, s->sell_soff, s->sell_len, s->sell_wi_start, s->sell_wi, s->sell_part,
-                    s->ypush, s->zpush, s->w0, s->aerr, s->aerr_t, s->ex, s->ety,
-                    s->aerr ? (void *)s->chc : nullptr, s->aerr ? (void *)s->bhc : nullptr};
+                    s->ypush,    s->zpush,    s->w0};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     if (s->st_host) (void)hipHostFree(s->st_host);
@@ -448,54 +443,52 @@ static int build_solver(int m, int n, int nz, const pdhg_params &p, const ModelS
         s->red_blocks_n = grid_for(n, kBlock, kMaxRedBlocks);
         const size_t vb = s->fp32 ? sizeof(float) : sizeof(double);
         const size_t M = (size_t)m, N = (size_t)n, NZ = (size_t)nz;
-        dalloc(&s->rp, M + 1);
-        dalloc(&s->ci, NZ);
-        dalloc(&s->av, NZ);
-        dalloc(&s->tp, N + 1);
-        dalloc(&s->ti, NZ);
-        dalloc(&s->tperm, NZ);
-        dalloc(&s->atv, NZ);
-        dalloc(&s->b, M);
-        dalloc(&s->c, N);
-        dalloc(&s->l, N);
-        dalloc(&s->u, N);
-        dalloc(&s->sense0, M);
-        dalloc(&s->sense, M);
-        dalloc(&s->dr, M);
-        dalloc(&s->dc, N);
-        auto vall = [&](void **ptr, size_t cnt) { hip_check(hipMalloc(ptr, vb * (cnt > 0 ? cnt : 1)), "hipMalloc"); };
-        vall(&s->ahat, NZ);
-        vall(&s->ahat_t, NZ);
-        for (void **q : {&s->x, &s->xbar, &s->lh, &s->uh}) vall(q, N);
-        for (void **q : {&s->xa, &s->xp, &s->xs}) // anchor, candidate, solution: float64
-            hip_check(hipMalloc(q, sizeof(double) * (N > 0 ? N : 1)), "hipMalloc");
-        dalloc(&s->ch, N);
-        for (void **q : {&s->y, &s->ya, &s->yp, &s->bh, &s->ys}) // m-vectors stay float64
-            hip_check(hipMalloc(q, sizeof(double) * (M > 0 ? M : 1)), "hipMalloc");
+        Slab slab;
+        auto vec = [&](void **q, size_t bytes) { slab.add(reinterpret_cast<char **>(q), bytes); };
+        slab.add(&s->rp, M + 1);
+        slab.add(&s->ci, NZ);
+        slab.add(&s->av, NZ);
+        slab.add(&s->tp, N + 1);
+        slab.add(&s->ti, NZ);
+        slab.add(&s->tperm, NZ);
+        slab.add(&s->atv, NZ);
+        slab.add(&s->b, M);
+        slab.add(&s->c, N);
+        slab.add(&s->l, N);
+        slab.add(&s->u, N);
+        slab.add(&s->sense0, M);
+        slab.add(&s->sense, M);
+        slab.add(&s->dr, M);
+        slab.add(&s->dc, N);
+        vec(&s->ahat, vb * NZ);
+        vec(&s->ahat_t, vb * NZ);
+        for (void **q : {&s->x, &s->xbar, &s->lh, &s->uh}) vec(q, vb * N);
+        for (void **q : {&s->xa, &s->xp, &s->xs}) vec(q, sizeof(double) * N); // anchor, candidate, solution: float64
+        slab.add(&s->ch, N);
+        for (void **q : {&s->y, &s->ya, &s->yp, &s->bh, &s->ys}) vec(q, sizeof(double) * M); // m-vectors stay float64
         if (s->fp32) { // the float matrix's rounding error, its products and the anchored data
-            hip_check(hipMalloc(&s->aerr, sizeof(float) * (NZ > 0 ? NZ : 1)), "hipMalloc");
-            hip_check(hipMalloc(&s->aerr_t, sizeof(float) * (NZ > 0 ? NZ : 1)), "hipMalloc");
-            dalloc(&s->ex, M);
-            dalloc(&s->ety, N);
-            dalloc(&s->chc, N);
-            dalloc(&s->bhc, M);
-        } else {
-            defect_alias(s);
+            vec(&s->aerr, sizeof(float) * NZ);
+            vec(&s->aerr_t, sizeof(float) * NZ);
+            slab.add(&s->ex, M);
+            slab.add(&s->ety, N);
+            slab.add(&s->chc, N);
+            slab.add(&s->bhc, M);
         }
-        dalloc(&s->ax, M);
-        dalloc(&s->aty, N);
-        dalloc(&s->xu, N);
-        dalloc(&s->yu, M);
-        dalloc(&s->zsol, N);
-        dalloc(&s->xpush, N);
-        const size_t nparts = (size_t)(Q_COUNT + 1) * (s->red_blocks_m + s->red_blocks_n) * 3 + 4 * kMaxRedBlocks;
-        dalloc(&s->partials, nparts);
+        slab.add(&s->ax, M);
+        slab.add(&s->aty, N);
+        slab.add(&s->xu, N);
+        slab.add(&s->yu, M);
+        slab.add(&s->zsol, N);
+        slab.add(&s->xpush, N);
+        slab.add(&s->partials, (size_t)(Q_COUNT + 1) * (s->red_blocks_m + s->red_blocks_n) * 3 + 4 * kMaxRedBlocks);
         if (p.record_history) {
-            dalloc(&s->hx, 4 * N);
-            dalloc(&s->hz, 4 * N);
+            slab.add(&s->hx, 4 * N);
+            slab.add(&s->hz, 4 * N);
         }
-        dalloc(&s->redout, 64);
-        dalloc(&s->st, 1);
+        slab.add(&s->redout, 64);
+        slab.add(&s->st, 1);
+        hip_check(slab.commit(&s->slab), "hipMalloc");
+        defect_alias(s);
         HIPCHK(hipHostMalloc((void **)&s->st_host, sizeof(DevState), hipHostMallocDefault));
         HIPCHK(hipHostMalloc((void **)&s->rep_host, sizeof(double) * 64, hipHostMallocDefault));
         HIPCHK(hipHostMalloc((void **)&s->cnt_host, sizeof(int64_t) * 16, hipHostMallocDefault));

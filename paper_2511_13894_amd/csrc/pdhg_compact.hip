@@ -189,18 +189,16 @@ __global__ __launch_bounds__(kBlock) void k_expand(int n, const int *__restrict_
 
 namespace {
 
-// out[0..len] = exclusive prefix sums of in[0..len] (in[len] = 0 gives out[len] = the total)
-hipError_t exclusive_scan(hipStream_t st, const int *in, int *out, int len)
+// scratch of an exclusive scan of len + 1 entries
+hipError_t scan_bytes(hipStream_t st, int len, size_t *bytes)
 {
-    size_t bytes = 0;
-    hipError_t e = hipcub::DeviceScan::ExclusiveSum(nullptr, bytes, in, out, len + 1, st);
-    if (e != hipSuccess) return e;
-    void *tmp = nullptr;
-    if ((e = hipMalloc(&tmp, bytes > 0 ? bytes : 1)) != hipSuccess) return e;
-    e = hipcub::DeviceScan::ExclusiveSum(tmp, bytes, in, out, len + 1, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    (void)hipFree(tmp);
-    return e;
+    return hipcub::DeviceScan::ExclusiveSum(nullptr, *bytes, (const int *)nullptr, (int *)nullptr, len + 1, st);
+}
+
+// out[0..len] = exclusive prefix sums of in[0..len] (in[len] = 0 gives out[len] = the total)
+hipError_t exclusive_scan(hipStream_t st, const int *in, int *out, int len, void *tmp, size_t bytes)
+{
+    return hipcub::DeviceScan::ExclusiveSum(tmp, bytes, in, out, len + 1, st);
 }
 
 int read_int(hipStream_t st, const int *p, hipError_t &e)
@@ -211,17 +209,9 @@ int read_int(hipStream_t st, const int *p, hipError_t &e)
     return v;
 }
 
-template <typename T>
-hipError_t alloc(T **p, size_t count)
-{
-    return hipMalloc(reinterpret_cast<void **>(p), sizeof(T) * (count > 0 ? count : 1));
-}
-
 void free_compact(pdhg_solver::PushCompact &c)
 {
-    void *ptrs[] = {c.flag, c.newid, c.keep, c.tp, c.ti, c.rp, c.ci, c.ahat, c.ahat_t, c.lh, c.uh,
-                    c.x, c.xa, c.xbar, c.xp, c.ch, c.dc, c.bt, c.lfix, c.l, c.u, c.aerr, c.aerr_t};
-    for (void *q : ptrs)
+    for (void *q : c.slabs)
         if (q) (void)hipFree(q);
     c = pdhg_solver::PushCompact{};
 }
@@ -233,13 +223,24 @@ hipError_t begin_impl(pdhg_solver *s)
     hipStream_t st = s->stream;
     const int n = s->n, m = s->m;
     const int gn1 = grid_for((int64_t)n + 1, kBlock, 1 << 30);
-    hipError_t e = alloc(&c.flag, (size_t)n + 1);
-    if (e == hipSuccess) e = alloc(&c.newid, (size_t)n + 1);
+    // column flags and index, and the scratch of the three scans (columns, kept columns, rows)
+    size_t scan = 0, scan_m = 0;
+    hipError_t e = scan_bytes(st, n, &scan);
+    if (e == hipSuccess) e = scan_bytes(st, m, &scan_m);
     if (e != hipSuccess) return e;
+    scan = scan > scan_m ? scan : scan_m;
+    char *tmp = nullptr;
+    int *cnt = nullptr;
+    Slab flags;
+    flags.add(&c.flag, (size_t)n + 1);
+    flags.add(&c.newid, (size_t)n + 1);
+    flags.add(&cnt, (size_t)(n > m ? n : m) + 1);
+    flags.add(&tmp, scan);
+    if ((e = flags.commit(&c.slabs[0])) != hipSuccess) return e;
     const int8_t *lfix = s->learned_active ? s->lfix : nullptr;
     hipLaunchKernelGGL((k_free_flags<V>), dim3(gn1), dim3(kBlock), 0, st, n, (const V *)s->lh, (const V *)s->uh, lfix,
                        c.flag);
-    if ((e = exclusive_scan(st, c.flag, c.newid, n)) != hipSuccess) return e;
+    if ((e = exclusive_scan(st, c.flag, c.newid, n, tmp, scan)) != hipSuccess) return e;
     const int nf = read_int(st, c.newid + n, e);
     if (e != hipSuccess) return e;
     if (nf == n) { // nothing fixed: iterate on the full model
@@ -247,53 +248,56 @@ hipError_t begin_impl(pdhg_solver *s)
         return hipSuccess;
     }
     c.nf = nf;
-    if ((e = alloc(&c.keep, (size_t)nf)) != hipSuccess) return e;
+    // transpose rows (the primal half) of the free columns, and the rows of A
+    // (the dual half) restricted to them: where they start
+    Slab starts;
+    starts.add(&c.keep, (size_t)nf);
+    starts.add(&c.tp, (size_t)nf + 1);
+    starts.add(&c.rp, (size_t)m + 1);
+    if ((e = starts.commit(&c.slabs[1])) != hipSuccess) return e;
     hipLaunchKernelGGL(k_keep_list, dim3(gn1), dim3(kBlock), 0, st, n, c.flag, c.newid, c.keep);
-    // transpose rows (the primal half) of the free columns
-    int *len = nullptr;
-    if ((e = alloc(&len, (size_t)nf + 1)) != hipSuccess) return e;
-    if ((e = alloc(&c.tp, (size_t)nf + 1)) != hipSuccess) {
-        (void)hipFree(len);
-        return e;
-    }
     hipLaunchKernelGGL(k_col_len, dim3(grid_for((int64_t)nf + 1, kBlock, 1 << 30)), dim3(kBlock), 0, st, nf, c.keep,
-                       s->tp, len);
-    e = exclusive_scan(st, len, c.tp, nf);
-    (void)hipFree(len);
-    if (e != hipSuccess) return e;
-    const int nnz_f = read_int(st, c.tp + nf, e);
-    if (e != hipSuccess) return e;
-    c.nnz = nnz_f;
-    if ((e = alloc(&c.ti, (size_t)nnz_f)) != hipSuccess) return e;
-    if ((e = alloc(reinterpret_cast<V **>(&c.ahat_t), (size_t)nnz_f)) != hipSuccess) return e;
-    hipLaunchKernelGGL((k_copy_cols<V>), dim3(grid_for(nf, kBlock, 1 << 30)), dim3(kBlock), 0, st, nf, c.keep, s->tp,
-                       s->ti, (const V *)s->ahat_t, c.tp, c.ti, (V *)c.ahat_t);
-    if (s->aerr) { // mixed mode: the free columns' rounding errors as well (same indices rewritten)
-        if ((e = alloc(reinterpret_cast<float **>(&c.aerr_t), (size_t)nnz_f)) != hipSuccess) return e;
-        hipLaunchKernelGGL((k_copy_cols<float>), dim3(grid_for(nf, kBlock, 1 << 30)), dim3(kBlock), 0, st, nf, c.keep,
-                           s->tp, s->ti, (const float *)s->aerr_t, c.tp, c.ti, (float *)c.aerr_t);
-    }
-    // rows of A (the dual half) restricted to the free columns
-    int *cnt = nullptr;
-    if ((e = alloc(&cnt, (size_t)m + 1)) != hipSuccess) return e;
-    if ((e = alloc(&c.rp, (size_t)m + 1)) != hipSuccess) {
-        (void)hipFree(cnt);
-        return e;
-    }
+                       s->tp, cnt);
+    if ((e = exclusive_scan(st, cnt, c.tp, nf, tmp, scan)) != hipSuccess) return e;
     const int gw = grid_for(((int64_t)m + 1) * 64, kBlock, 1 << 30); // one wave per row
     hipLaunchKernelGGL(k_row_free_count, dim3(gw), dim3(kBlock), 0, st, m, s->rp, s->ci, c.flag, cnt);
-    e = exclusive_scan(st, cnt, c.rp, m);
-    (void)hipFree(cnt);
-    if (e != hipSuccess) return e;
+    if ((e = exclusive_scan(st, cnt, c.rp, m, tmp, scan)) != hipSuccess) return e;
+    const int nnz_f = read_int(st, c.tp + nf, e);
     const int nnz_rows = read_int(st, c.rp + m, e);
     if (e != hipSuccess) return e;
     if (nnz_rows != nnz_f) return hipErrorInvalidValue; // A and its transpose disagree
-    if ((e = alloc(&c.ci, (size_t)nnz_f)) != hipSuccess) return e;
-    if ((e = alloc(reinterpret_cast<V **>(&c.ahat), (size_t)nnz_f)) != hipSuccess) return e;
+    c.nnz = nnz_f;
+    Slab rest;
+    const size_t NF = (size_t)nf, NZ = (size_t)nnz_f;
+    rest.add(&c.ti, NZ);
+    rest.add(reinterpret_cast<V **>(&c.ahat_t), NZ);
+    rest.add(&c.ci, NZ);
+    rest.add(reinterpret_cast<V **>(&c.ahat), NZ);
+    if (s->aerr) { // mixed mode: the free columns' rounding errors as well
+        rest.add(reinterpret_cast<float **>(&c.aerr_t), NZ);
+        rest.add(reinterpret_cast<float **>(&c.aerr), NZ);
+    }
+    rest.add(&c.bt, (size_t)m);
+    rest.add(&c.ch, NF);
+    rest.add(&c.dc, NF);
+    for (V **q : {reinterpret_cast<V **>(&c.lh), reinterpret_cast<V **>(&c.uh), reinterpret_cast<V **>(&c.x),
+                  reinterpret_cast<V **>(&c.xbar)})
+        rest.add(q, NF);
+    for (double **q : {reinterpret_cast<double **>(&c.xa), reinterpret_cast<double **>(&c.xp)}) // float64 anchor, candidate
+        rest.add(q, NF);
+    if (lfix) {
+        rest.add(&c.lfix, NF);
+        rest.add(&c.l, NF);
+        rest.add(&c.u, NF);
+    }
+    if ((e = rest.commit(&c.slabs[2])) != hipSuccess) return e;
+    hipLaunchKernelGGL((k_copy_cols<V>), dim3(grid_for(nf, kBlock, 1 << 30)), dim3(kBlock), 0, st, nf, c.keep, s->tp,
+                       s->ti, (const V *)s->ahat_t, c.tp, c.ti, (V *)c.ahat_t);
     hipLaunchKernelGGL((k_copy_rows<V>), dim3(gw), dim3(kBlock), 0, st, m, s->rp, s->ci, (const V *)s->ahat, c.flag,
                        c.newid, c.rp, c.ci, (V *)c.ahat);
-    if (s->aerr) {
-        if ((e = alloc(reinterpret_cast<float **>(&c.aerr), (size_t)nnz_f)) != hipSuccess) return e;
+    if (s->aerr) { // the same indices rewritten
+        hipLaunchKernelGGL((k_copy_cols<float>), dim3(grid_for(nf, kBlock, 1 << 30)), dim3(kBlock), 0, st, nf, c.keep,
+                           s->tp, s->ti, (const float *)s->aerr_t, c.tp, c.ti, (float *)c.aerr_t);
         hipLaunchKernelGGL((k_copy_rows<float>), dim3(gw), dim3(kBlock), 0, st, m, s->rp, s->ci,
                            (const float *)s->aerr, c.flag, c.newid, c.rp, c.ci, (float *)c.aerr);
     }
@@ -301,26 +305,14 @@ hipError_t begin_impl(pdhg_solver *s)
     double *xf = s->aty;
     hipLaunchKernelGGL((k_fixed_values<V>), dim3(gn1), dim3(kBlock), 0, st, n, c.flag, (const V *)s->lh, xf);
     if ((e = exact_product(s, false, xf, s->ax)) != hipSuccess) return e;
-    if ((e = alloc(&c.bt, (size_t)m)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_btilde, dim3(grid_for(m, kBlock, 1 << 30)), dim3(kBlock), 0, st, m, (const double *)s->bh,
                        s->ax, c.bt);
     // the free columns' vectors
-    if ((e = alloc(&c.ch, (size_t)nf)) != hipSuccess) return e;
-    if ((e = alloc(&c.dc, (size_t)nf)) != hipSuccess) return e;
-    V **vecs[] = {reinterpret_cast<V **>(&c.lh), reinterpret_cast<V **>(&c.uh), reinterpret_cast<V **>(&c.x),
-                  reinterpret_cast<V **>(&c.xbar)};
-    for (V **q : vecs)
-        if ((e = alloc(q, (size_t)nf)) != hipSuccess) return e;
-    for (double **q : {reinterpret_cast<double **>(&c.xa), reinterpret_cast<double **>(&c.xp)}) // float64 anchor, candidate
-        if ((e = alloc(q, (size_t)nf)) != hipSuccess) return e;
     hipLaunchKernelGGL((k_gather_free<V>), dim3(grid_for(nf, kBlock, 1 << 30)), dim3(kBlock), 0, st, nf, c.keep,
                        s->ch, s->dc, (const V *)s->lh, (const V *)s->uh, (const V *)s->x, (const double *)s->xa,
                        (const double *)s->xp, c.ch, c.dc, (V *)c.lh, (V *)c.uh, (V *)c.x, (double *)c.xa,
                        (double *)c.xp);
     if (lfix) {
-        if ((e = alloc(&c.lfix, (size_t)nf)) != hipSuccess) return e;
-        if ((e = alloc(&c.l, (size_t)nf)) != hipSuccess) return e;
-        if ((e = alloc(&c.u, (size_t)nf)) != hipSuccess) return e;
         hipLaunchKernelGGL(k_gather_learned, dim3(grid_for(nf, kBlock, 1 << 30)), dim3(kBlock), 0, st, nf, c.keep, lfix,
                            s->l, s->u, c.lfix, c.l, c.u);
     }

@@ -6,6 +6,7 @@
 
 #include <cstdint>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "pdhg.h"
@@ -21,6 +22,32 @@
     } while (0)
 
 namespace pdhg {
+
+// Several device arrays in one allocation.  Freeing an array of more than a
+// megabyte costs about 0.23 ms and allocating it 0.04 ms, whatever its size
+// (60 arrays of 20 MB: 13.9 and 1.7 ms; one of 1.2 GB: 0.30 and 0.08 ms), so a
+// solver's arrays, a phase's temporaries and the push model share one each.
+class Slab {
+public:
+    template <typename T>
+    void add(T **ptr, size_t count)
+    {
+        want_.push_back({reinterpret_cast<void **>(ptr), total_});
+        total_ += (sizeof(T) * (count > 0 ? count : 1) + 255) / 256 * 256;
+    }
+    // the allocation (*base, to be freed by the caller) and every array's pointer into it
+    hipError_t commit(void **base)
+    {
+        const hipError_t e = hipMalloc(base, total_ > 0 ? total_ : 1);
+        if (e == hipSuccess)
+            for (const auto &w : want_) *w.first = static_cast<char *>(*base) + w.second;
+        return e;
+    }
+
+private:
+    std::vector<std::pair<void **, size_t>> want_;
+    size_t total_ = 0;
+};
 
 constexpr int kBlock = 256;         // threads per workgroup (4 wave64)
 constexpr int kRowBlock = -2256; // kernel code: one row per workgroup of kBlock threads
@@ -102,6 +129,7 @@ struct pdhg_solver {
     bool own_stream = false;
     bool lone = false; // one LP of its own, not the model of a batch
     bool fp32 = false;
+    void *slab = nullptr; // the arrays below that exist for every handle, in one allocation
 
     // original model, float64, row-compressed A and its explicit transpose
     int *rp = nullptr, *ci = nullptr;
@@ -201,6 +229,7 @@ struct pdhg_solver {
     // replace in this struct until the push ends
     struct PushCompact {
         bool active = false;
+        void *slabs[3] = {}; // the arrays below: column flags, then column pointers, then the rest
         int nf = 0, nnz = 0;
         int *flag = nullptr, *newid = nullptr, *keep = nullptr; // free flag and index of every full column; full index of each compact one
         int *tp = nullptr, *ti = nullptr, *rp = nullptr, *ci = nullptr;

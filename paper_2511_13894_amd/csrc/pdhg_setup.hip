@@ -320,24 +320,23 @@ hipError_t batch_assemble_device(hipStream_t st, const std::vector<BatchPart> &p
         max_n = q.n > max_n ? q.n : max_n;
         max_nz = q.nnz > max_nz ? q.nnz : max_nz;
     }
-    auto get = [&](void **ptr, size_t bytes) {
-        hipError_t e = hipMalloc(ptr, bytes > 0 ? bytes : 1);
-        if (e == hipSuccess) temps.push_back(*ptr);
-        return e;
-    };
     void *rp = nullptr, *ci = nullptr, *val = nullptr, *b = nullptr, *c = nullptr, *l = nullptr, *u = nullptr,
-         *sense = nullptr, *d_parts = nullptr, *d_bad = nullptr;
-    hipError_t e = get(&rp, sizeof(int64_t) * ((size_t)M + 1));
-    if (e == hipSuccess) e = get(&ci, sizeof(int32_t) * (size_t)NZ);
-    if (e == hipSuccess) e = get(&val, sizeof(double) * (size_t)NZ);
-    if (e == hipSuccess) e = get(&b, sizeof(double) * (size_t)M);
-    if (e == hipSuccess) e = get(&sense, (size_t)M);
-    if (e == hipSuccess) e = get(&c, sizeof(double) * (size_t)N);
-    if (e == hipSuccess) e = get(&l, sizeof(double) * (size_t)N);
-    if (e == hipSuccess) e = get(&u, sizeof(double) * (size_t)N);
-    if (e == hipSuccess) e = get(&d_parts, sizeof(BatchPart) * (size_t)count);
-    if (e == hipSuccess) e = get(&d_bad, sizeof(unsigned));
+         *sense = nullptr, *d_parts = nullptr, *d_bad = nullptr, *temp = nullptr;
+    Slab slab;
+    auto get = [&](void **ptr, size_t bytes) { slab.add(reinterpret_cast<char **>(ptr), bytes); };
+    get(&rp, sizeof(int64_t) * ((size_t)M + 1));
+    get(&ci, sizeof(int32_t) * (size_t)NZ);
+    get(&val, sizeof(double) * (size_t)NZ);
+    get(&b, sizeof(double) * (size_t)M);
+    get(&sense, (size_t)M);
+    get(&c, sizeof(double) * (size_t)N);
+    get(&l, sizeof(double) * (size_t)N);
+    get(&u, sizeof(double) * (size_t)N);
+    get(&d_parts, sizeof(BatchPart) * (size_t)count);
+    get(&d_bad, sizeof(unsigned));
+    hipError_t e = slab.commit(&temp);
     if (e != hipSuccess) return e;
+    temps.push_back(temp);
     e = hipMemcpyAsync(d_parts, parts.data(), sizeof(BatchPart) * (size_t)count, hipMemcpyHostToDevice, st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(1), 0, st, (unsigned *)d_bad, 0u);
@@ -378,12 +377,14 @@ hipError_t build_transpose(pdhg_solver *s)
     const int tiles = (n + kScanTile - 1) / kScanTile;
     int *rowid = nullptr, *cnt = nullptr, *ti_u = nullptr, *perm_u = nullptr, *work = nullptr;
     hipError_t e = hipSuccess;
-    size_t nz = (size_t)(nnz > 0 ? nnz : 1);
-    if ((e = hipMalloc(&rowid, nz * sizeof(int))) != hipSuccess) return e;
-    if ((e = hipMalloc(&cnt, (size_t)(n + 1) * sizeof(int))) != hipSuccess) return e;
-    if ((e = hipMalloc(&ti_u, nz * sizeof(int))) != hipSuccess) return e;
-    if ((e = hipMalloc(&perm_u, nz * sizeof(int))) != hipSuccess) return e;
-    if ((e = hipMalloc(&work, (size_t)(tiles + 2) * sizeof(int))) != hipSuccess) return e;
+    Slab slab;
+    void *temp = nullptr;
+    slab.add(&rowid, (size_t)nnz);
+    slab.add(&cnt, (size_t)n + 1);
+    slab.add(&ti_u, (size_t)nnz);
+    slab.add(&perm_u, (size_t)nnz);
+    slab.add(&work, (size_t)tiles + 2);
+    if ((e = slab.commit(&temp)) != hipSuccess) return e;
     hipMemsetAsync(cnt, 0, (size_t)(n + 1) * sizeof(int), st);
     const int big = grid_for(nnz, kBlock, 65536);
     if (m > 0) hipLaunchKernelGGL(k_rowid, dim3(grid_for((int64_t)m * 64, kBlock, 1 << 30)), dim3(kBlock), 0, st, m, s->rp, rowid);
@@ -398,11 +399,7 @@ hipError_t build_transpose(pdhg_solver *s)
     }
     e = hipGetLastError();
     hipError_t e2 = hipStreamSynchronize(st);
-    hipFree(rowid);
-    hipFree(cnt);
-    hipFree(ti_u);
-    hipFree(perm_u);
-    hipFree(work);
+    (void)hipFree(temp);
     return e != hipSuccess ? e : e2;
 }
 
@@ -523,12 +520,14 @@ hipError_t scale_problem(pdhg_solver *s)
     double *ah = nullptr, *aht = nullptr, *r = nullptr, *q = nullptr;
     int *rowid = nullptr;
     hipError_t e;
-    size_t nz = (size_t)(nnz > 0 ? nnz : 1);
-    if ((e = hipMalloc(&ah, nz * sizeof(double))) != hipSuccess) return e;
-    if ((e = hipMalloc(&aht, nz * sizeof(double))) != hipSuccess) return e;
-    if ((e = hipMalloc(&r, (size_t)(m > 0 ? m : 1) * sizeof(double))) != hipSuccess) return e;
-    if ((e = hipMalloc(&q, (size_t)(n > 0 ? n : 1) * sizeof(double))) != hipSuccess) return e;
-    if ((e = hipMalloc(&rowid, nz * sizeof(int))) != hipSuccess) return e;
+    Slab slab;
+    void *temp = nullptr;
+    slab.add(&ah, (size_t)nnz);
+    slab.add(&aht, (size_t)nnz);
+    slab.add(&r, (size_t)m);
+    slab.add(&q, (size_t)n);
+    slab.add(&rowid, (size_t)nnz);
+    if ((e = slab.commit(&temp)) != hipSuccess) return e;
     hipMemcpyAsync(ah, s->av, (size_t)nnz * sizeof(double), hipMemcpyDeviceToDevice, st);
     if (m > 0) hipLaunchKernelGGL(k_rowid, dim3(grid_for((int64_t)m * 64, kBlock, 1 << 30)), dim3(kBlock), 0, st, m, s->rp, rowid);
     hipLaunchKernelGGL(k_fill, dim3(grid_for(m, kBlock, 4096)), dim3(kBlock), 0, st, (int64_t)m, s->dr, 1.0);
@@ -555,11 +554,7 @@ hipError_t scale_problem(pdhg_solver *s)
     else make_scaled<double>(s, ah);
     e = hipGetLastError();
     hipError_t e2 = hipStreamSynchronize(st);
-    hipFree(ah);
-    hipFree(aht);
-    hipFree(r);
-    hipFree(q);
-    hipFree(rowid);
+    (void)hipFree(temp);
     return e != hipSuccess ? e : e2;
 }
 
@@ -643,14 +638,20 @@ hipError_t power_iteration(pdhg_solver *s)
     const int m = s->m, n = s->n;
     double *v = nullptr, *w = nullptr, *u = nullptr, *pw = nullptr;
     hipError_t e;
-    if ((e = hipMalloc(&v, (size_t)(n > 0 ? n : 1) * sizeof(double))) != hipSuccess) return e;
-    if ((e = hipMalloc(&w, (size_t)(n > 0 ? n : 1) * sizeof(double))) != hipSuccess) return e;
-    if ((e = hipMalloc(&u, (size_t)(m > 0 ? m : 1) * sizeof(double))) != hipSuccess) return e;
-    if ((e = hipMalloc(&pw, 4 * sizeof(double))) != hipSuccess) return e;
+    Slab slab;
+    void *temp = nullptr;
+    slab.add(&v, (size_t)n);
+    slab.add(&w, (size_t)n);
+    slab.add(&u, (size_t)m);
+    slab.add(&pw, 4);
+    if ((e = slab.commit(&temp)) != hipSuccess) return e;
     hipMemsetAsync(pw, 0, 4 * sizeof(double), st);
     const int gm = grid_for(m, kBlock, kMaxRedBlocks), gn = grid_for(n, kBlock, kMaxRedBlocks);
     const bool resident = s->res.variant > 0; // a small LP's steps in one launch
-    if (resident && (e = resident_power(s, pw)) != hipSuccess) return e;
+    if (resident && (e = resident_power(s, pw)) != hipSuccess) {
+        (void)hipFree(temp);
+        return e;
+    }
     if (n > 0 && !resident) { // start: v = (1 + U) / ||1 + U||, the norm kept in pw[3]
         const int gv = grid_for(n, kBlock, 1 << 30);
         hipLaunchKernelGGL(k_power_start, dim3(gv), dim3(kBlock), 0, st, (int64_t)n, v);
@@ -682,10 +683,7 @@ hipError_t power_iteration(pdhg_solver *s)
         e = hipGetLastError();
     }
     hipError_t e2 = hipStreamSynchronize(st);
-    hipFree(v);
-    hipFree(w);
-    hipFree(u);
-    hipFree(pw);
+    (void)hipFree(temp);
     return e != hipSuccess ? e : e2;
 }
 
