@@ -127,67 +127,75 @@ __device__ __forceinline__ int xcd_block(int bid, int nblk)
 }
 
 // One lane's share of a row's product: the terms e = beg+lane, beg+lane+L, ...
-// below end, accumulated in that order, in rounds of four.  A lane's share is
-// a chain of loads (index, then operand); a round's gathers go out together,
+// below end, accumulated in that order, in rounds of U.  A lane's share is a
+// chain of loads (index, then operand); a round's gathers go out together,
 // and before they are waited for the next round's index and value loads, so a
 // round costs one gather's latency and the index loads hide behind it.
 // Positions past the end reload the last entry; their terms are not added.
-// Iterations of transportation LPs, rounds without the overlap -> with it:
-// 200x500 8.53 -> 7.96 us (mixed 8.24 -> 7.49), 1000x2500 49.9 -> 49.5
-// (mixed 40.7 -> 36.0); 2000x5000, bound by its 20 million entries' bytes,
-// 169 -> 172 in the solve and 13.2 -> 13.1 in the push.
-template <int L, typename ACC, typename I, typename VM, typename VX>
-__device__ __forceinline__ ACC lane_dot(int beg, int end, int lane, const I *__restrict__ idx,
-                                        const VM *__restrict__ val, const VX *__restrict__ x)
+template <int L, int U, typename ACC, typename I, typename VM, typename VX>
+__device__ __forceinline__ ACC lane_rounds(int beg, int end, int lane, const I *__restrict__ idx,
+                                           const VM *__restrict__ val, const VX *__restrict__ x)
 {
     ACC acc = 0;
     int e = beg + lane;
     if (e >= end) return acc;
     const int last = end - 1;
-    int c1 = e + L < last ? e + L : last, c2 = e + 2 * L < last ? e + 2 * L : last, c3 = e + 3 * L < last ? e + 3 * L : last;
-    I i0 = idx[e], i1 = idx[c1], i2 = idx[c2], i3 = idx[c3];
-    VM v0 = val[e], v1 = val[c1], v2 = val[c2], v3 = val[c3];
+    I i[U];
+    VM v[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        const int k = e + u * L < last ? e + u * L : last;
+        i[u] = idx[k];
+        v[u] = val[k];
+    }
     for (;;) {
-        const VX g0 = x[i0], g1 = x[i1], g2 = x[i2], g3 = x[i3];
-        const ACC w0 = (ACC)v0, w1 = (ACC)v1, w2 = (ACC)v2, w3 = (ACC)v3;
-        const int n0 = e + 4 * L;
-        if (!__builtin_amdgcn_ballot_w64(n0 + 3 * L >= end)) { // a full round for every lane of the wave still here
-            i0 = idx[n0];
-            i1 = idx[n0 + L];
-            i2 = idx[n0 + 2 * L];
-            i3 = idx[n0 + 3 * L];
-            v0 = val[n0];
-            v1 = val[n0 + L];
-            v2 = val[n0 + 2 * L];
-            v3 = val[n0 + 3 * L];
-            acc += w0 * (ACC)g0;
-            acc += w1 * (ACC)g1;
-            acc += w2 * (ACC)g2;
-            acc += w3 * (ACC)g3;
+        VX g[U];
+        ACC w[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) g[u] = x[i[u]];
+#pragma unroll
+        for (int u = 0; u < U; u++) w[u] = (ACC)v[u];
+        const int n0 = e + U * L;
+        if (!__builtin_amdgcn_ballot_w64(n0 + (U - 1) * L >= end)) { // a full round for every lane of the wave still here
+#pragma unroll
+            for (int u = 0; u < U; u++) i[u] = idx[n0 + u * L];
+#pragma unroll
+            for (int u = 0; u < U; u++) v[u] = val[n0 + u * L];
+#pragma unroll
+            for (int u = 0; u < U; u++) acc += w[u] * (ACC)g[u];
             e = n0;
             continue;
         }
         if (__builtin_amdgcn_ballot_w64(n0 < end)) {
-            const int c0 = n0 < last ? n0 : last;
-            c1 = n0 + L < last ? n0 + L : last;
-            c2 = n0 + 2 * L < last ? n0 + 2 * L : last;
-            c3 = n0 + 3 * L < last ? n0 + 3 * L : last;
-            i0 = idx[c0];
-            i1 = idx[c1];
-            i2 = idx[c2];
-            i3 = idx[c3];
-            v0 = val[c0];
-            v1 = val[c1];
-            v2 = val[c2];
-            v3 = val[c3];
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                const int k = n0 + u * L < last ? n0 + u * L : last;
+                i[u] = idx[k];
+                v[u] = val[k];
+            }
         }
-        acc += w0 * (ACC)g0;
-        if (e + L < end) acc += w1 * (ACC)g1;
-        if (e + 2 * L < end) acc += w2 * (ACC)g2;
-        if (e + 3 * L < end) acc += w3 * (ACC)g3;
+        acc += w[0] * (ACC)g[0];
+#pragma unroll
+        for (int u = 1; u < U; u++)
+            if (e + u * L < end) acc += w[u] * (ACC)g[u];
         if (n0 >= end) return acc;
         e = n0;
     }
+}
+
+// Rounds of eight where a row of the wave has more than four entries a lane:
+// fewer waits in a chain; at most four entries: rounds of four, as the other
+// four loads would repeat the last entry.  Per iteration on transportation
+// LPs (fp64 / mixed), rounds of four -> this rule: 200x500 7.33 / 6.97 -> 6.94
+// / 6.55 us, 1000x2500 46.8 / 35.6 -> 46.9 / 33.6; 2000x5000 228.7 / 159.2 ->
+// 225.8 / 158.9 in the solve, 16.3 / 12.8 -> 16.2 / 12.6 in the push (12.9
+// with rounds of eight alone: its sink rows have three entries a lane).
+template <int L, typename ACC, typename I, typename VM, typename VX>
+__device__ __forceinline__ ACC lane_dot(int beg, int end, int lane, const I *__restrict__ idx,
+                                        const VM *__restrict__ val, const VX *__restrict__ x)
+{
+    if (__builtin_amdgcn_ballot_w64(end - beg > 4 * L)) return lane_rounds<L, 8, ACC>(beg, end, lane, idx, val, x);
+    return lane_rounds<L, 4, ACC>(beg, end, lane, idx, val, x);
 }
 
 // Row-compressed product out[r] = sum_e val[e] * x[idx[e]] over rows r < rows,

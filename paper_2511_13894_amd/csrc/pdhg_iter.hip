@@ -41,7 +41,7 @@ __global__ __launch_bounds__(kBlock) void k_primal(int n, const int *__restrict_
 
 // Dual half on rows [row0, row1), one row of A per group of L lanes, for the
 // workgroup that takes logical block lb:  h = Ahat xbar, then the update.
-template <typename V, int L>
+template <typename V, int L, int NT>
 __device__ __forceinline__ void dual_rows(int row0, int row1, int lb, const int *__restrict__ rp,
                                           const int *__restrict__ ci, const V *__restrict__ av,
                                           const V *__restrict__ xbar, const double *__restrict__ bh,
@@ -49,7 +49,7 @@ __device__ __forceinline__ void dual_rows(int row0, int row1, int lb, const int 
                                           const double *__restrict__ ya, double *__restrict__ yp,
                                           const DevState *__restrict__ st, int i, int store_cand)
 {
-    const int64_t gi = (int64_t)lb * kBlock + threadIdx.x;
+    const int64_t gi = (int64_t)lb * NT + threadIdx.x;
     const int64_t r = row0 + gi / L;
     const int lane = (int)(gi % L);
     if (r >= row1) return;
@@ -72,7 +72,7 @@ __global__ __launch_bounds__(kBlock) void k_dual(int m, const int *__restrict__ 
                                                 double *__restrict__ yp, const DevState *__restrict__ st, int i,
                                                 int store_cand)
 {
-    dual_rows<V, L>(0, m, xcd_block(blockIdx.x, gridDim.x), rp, ci, av, xbar, bh, sense, y, ya, yp, st, i,
+    dual_rows<V, L, kBlock>(0, m, xcd_block(blockIdx.x, gridDim.x), rp, ci, av, xbar, bh, sense, y, ya, yp, st, i,
                     store_cand);
 }
 
@@ -85,7 +85,13 @@ __global__ __launch_bounds__(kBlock) void k_dual(int m, const int *__restrict__ 
 // groups put more such rows in a workgroup, whose shared L1 then serves them.
 // Each segment has its own workgroups in one launch; a workgroup finds its
 // segment from its index (a uniform branch) and maps itself onto the XCDs
-// as a launch of the segment alone would.
+// as a launch of the segment alone would.  A workgroup is one wave: rows need
+// nothing from each other, so a wave's place is free for the next one as soon
+// as its own rows are done, and the last rows of a launch spread over more
+// CUs.  Per iteration on transportation LPs (fp64 / mixed), workgroups of 256
+// threads -> 64: 200x500 7.86 / 7.36 -> 7.33 / 6.98 us, 1000x2500 49.8 / 36.0
+// -> 46.7 / 35.7, 2000x5000 238.9 / 172.2 -> 228.4 / 159.1 in the solve and
+// 16.8 / 13.05 -> 16.3 / 12.87 in the push (128 threads between, 512 slower).
 __device__ __forceinline__ int seg_of(const RowSegs &sg, int b)
 {
     int k = 0;
@@ -94,7 +100,7 @@ __device__ __forceinline__ int seg_of(const RowSegs &sg, int b)
 }
 
 template <typename V>
-__global__ __launch_bounds__(kBlock) void k_dual_segs(RowSegs sg, const int *__restrict__ rp,
+__global__ __launch_bounds__(kSegBlock) void k_dual_segs(RowSegs sg, const int *__restrict__ rp,
                                                      const int *__restrict__ ci, const V *__restrict__ av,
                                                      const V *__restrict__ xbar, const double *__restrict__ bh,
                                                      const int8_t *__restrict__ sense, double *__restrict__ y,
@@ -106,7 +112,7 @@ __global__ __launch_bounds__(kBlock) void k_dual_segs(RowSegs sg, const int *__r
     const int r0 = sg.row0[k], r1 = sg.row0[k + 1];
 #define PDHG_SEG_CASE(LL)                                                                                       \
     case LL:                                                                                                    \
-        dual_rows<V, LL>(r0, r1, lb, rp, ci, av, xbar, bh, sense, y, ya, yp, st, i, store_cand);               \
+        dual_rows<V, LL, kSegBlock>(r0, r1, lb, rp, ci, av, xbar, bh, sense, y, ya, yp, st, i, store_cand);               \
         break;
     switch (sg.lanes[k]) {
         PDHG_SEG_CASE(1)
@@ -122,12 +128,12 @@ __global__ __launch_bounds__(kBlock) void k_dual_segs(RowSegs sg, const int *__r
 }
 
 // out = M vec on the same segments (the check products of this dual half)
-template <typename VM, typename VV, int L>
+template <typename VM, typename VV, int L, int NT>
 __device__ __forceinline__ void spmv_rows(int row0, int row1, int lb, const int *__restrict__ ptr,
                                           const int *__restrict__ idx, const VM *__restrict__ val,
                                           const VV *__restrict__ vec, double *__restrict__ out)
 {
-    const int64_t gi = (int64_t)lb * kBlock + threadIdx.x;
+    const int64_t gi = (int64_t)lb * NT + threadIdx.x;
     const int64_t r = row0 + gi / L;
     const int lane = (int)(gi % L);
     if (r >= row1) return;
@@ -137,7 +143,7 @@ __device__ __forceinline__ void spmv_rows(int row0, int row1, int lb, const int 
 }
 
 template <typename VM, typename VV>
-__global__ __launch_bounds__(kBlock) void k_spmv_segs(RowSegs sg, const int *__restrict__ ptr,
+__global__ __launch_bounds__(kSegBlock) void k_spmv_segs(RowSegs sg, const int *__restrict__ ptr,
                                                      const int *__restrict__ idx, const VM *__restrict__ val,
                                                      const VV *__restrict__ vec, double *__restrict__ out)
 {
@@ -146,7 +152,7 @@ __global__ __launch_bounds__(kBlock) void k_spmv_segs(RowSegs sg, const int *__r
     const int r0 = sg.row0[k], r1 = sg.row0[k + 1];
 #define PDHG_SEG_CASE(LL)                                                                                       \
     case LL:                                                                                                    \
-        spmv_rows<VM, VV, LL>(r0, r1, lb, ptr, idx, val, vec, out);                                            \
+        spmv_rows<VM, VV, LL, kSegBlock>(r0, r1, lb, ptr, idx, val, vec, out);                                            \
         break;
     switch (sg.lanes[k]) {
         PDHG_SEG_CASE(1)
@@ -287,7 +293,7 @@ static void row_product(const pdhg_solver *s, const VM *val, const VV *vec, doub
     if (s->m <= 0) return;
     if (s->kern_a == kRowSegs) {
         const RowSegs &sg = s->segs;
-        hipLaunchKernelGGL((k_spmv_segs<VM, VV>), dim3(sg.blk0[sg.count]), dim3(kBlock), 0, s->stream, sg, s->rp,
+        hipLaunchKernelGGL((k_spmv_segs<VM, VV>), dim3(sg.blk0[sg.count]), dim3(kSegBlock), 0, s->stream, sg, s->rp,
                            s->ci, val, vec, out);
         return;
     }
@@ -560,7 +566,7 @@ static void launch_dual(pdhg_solver *s, int i, int store, hipEvent_t e0 = nullpt
     }
     if (L == kRowSegs) {
         const RowSegs &sg = s->segs;
-        PDHG_LAUNCH(e0, e1, (k_dual_segs<V>), dim3(sg.blk0[sg.count]), dim3(kBlock), s->stream, sg, s->rp, s->ci,
+        PDHG_LAUNCH(e0, e1, (k_dual_segs<V>), dim3(sg.blk0[sg.count]), dim3(kSegBlock), s->stream, sg, s->rp, s->ci,
                     (const V *)s->ahat, (const V *)s->xbar, (const double *)s->bhc, s->sense, (double *)s->y,
                     (const double *)s->ya, (double *)s->yp, s->st, i, store);
         return;
@@ -1614,7 +1620,7 @@ static RowSegs row_segments(const std::vector<int> &rp, const std::vector<int> &
         else if (cls[k] == 0 && mean >= 512.0) w = 16;
         sg.row0[k] = r0;
         sg.lanes[k] = w;
-        const int64_t blocks = ((int64_t)(r1 - r0) * w + kBlock - 1) / kBlock;
+        const int64_t blocks = ((int64_t)(r1 - r0) * w + kSegBlock - 1) / kSegBlock;
         sg.blk0[k + 1] = sg.blk0[k] + (int)((blocks + 7) / 8 * 8);
     }
     sg.row0[sg.count] = m;

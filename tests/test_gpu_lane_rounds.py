@@ -1,4 +1,4 @@
-"""The lane-group products at the edges of their rounds of four entries a
+"""The lane-group products at the edges of their rounds of four and eight entries a
 lane: rows of no entry, of less than one round, of exactly one, two and three
 and of one entry more or less, neighbours in a wave ending in different
 rounds, in both halves, against the oracle."""
@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 def _lp(lanes, transposed):
-    lens = [0] + [k * lanes + d for k in (1, 2, 3, 4, 5, 7, 8, 9, 12) for d in (-1, 0, 1)]
+    lens = [0] + [k * lanes + d for k in (1, 2, 3, 4, 5, 7, 8, 9, 12, 16, 24) for d in (-1, 0, 1)]
     a = np.zeros((len(lens), max(lens) + 3))
     rng = np.random.default_rng(lanes)
     for r in rng.permutation(len(lens)):
@@ -29,7 +29,7 @@ def _lp(lanes, transposed):
 def test_lane_rounds_follow_the_oracle(lanes, precision):
     # fp64: the bound of the other iterate tests.  fp32 rounds the matrix and
     # the differences it sums to 24 bits, at most 2^-24 a term: over 5
-    # iterations of rows with up to 770 entries of mixed sign, 1e-4.
+    # iterations of rows with up to 1,537 entries of mixed sign, 1e-4.
     tol = 1e-10 if precision == "fp64" else 1e-4
     for transposed in (False, True):
         if lanes == -4000:
