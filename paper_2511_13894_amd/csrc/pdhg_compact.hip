@@ -322,6 +322,9 @@ hipError_t begin_impl(pdhg_solver *s)
     c.n0 = s->n;
     c.nnz0 = s->nnz;
     c.udeg_at0 = s->udeg_at;
+    c.longest_col0 = s->longest_col;
+    c.longest_row0 = s->longest_row;
+    c.beside0 = s->beside;
     c.red_blocks_n0 = s->red_blocks_n;
     c.tp0 = s->tp;
     c.ti0 = s->ti;
@@ -383,7 +386,7 @@ hipError_t begin_impl(pdhg_solver *s)
         s->graph_mode = -1;
     }
     if (s->kern_a == kRowSegs && (e = plan_row_segments(s)) != hipSuccess) return e; // of the compact rows
-    if ((e = detect_uniform_columns(s)) != hipSuccess) return e; // of the compact model (on failure the caller restores the full one)
+    if ((e = row_shapes(s)) != hipSuccess) return e; // of the compact model (on failure the caller restores the full one)
     return resident_plan(s);
 }
 
@@ -402,6 +405,9 @@ hipError_t end_impl(pdhg_solver *s, bool scatter)
     s->n = c.n0;
     s->nnz = c.nnz0;
     s->udeg_at = c.udeg_at0;
+    s->longest_col = c.longest_col0;
+    s->longest_row = c.longest_row0;
+    s->beside = c.beside0;
     s->red_blocks_n = c.red_blocks_n0;
     s->tp = c.tp0;
     s->ti = c.ti0;

@@ -182,6 +182,8 @@ struct pdhg_solver {
 
     int lanes_at = 1, lanes_a = 1; // lane-group width of setup / check products
     int udeg_at = 0;               // every column holds this many entries (1..3), else 0
+    int longest_col = 0, longest_row = 0; // entries of the longest column and row of the current model
+    int beside = 0;                // entries of its rows that gather next to the row before them (row_shapes)
     int kern_at = 1, kern_a = 1;   // iteration kernels: > 0 lane-group width, < 0 LDS tile of -k rows
     pdhg::RowSegs segs;            // the dual half's row segments (kern_a == kRowSegs)
     // a small LP's iterations in one workgroup: kernel variant (0: none), the
@@ -240,7 +242,8 @@ struct pdhg_solver {
         void *aerr = nullptr, *aerr_t = nullptr; // mixed precision: the free columns' matrix errors
         int8_t *lfix = nullptr;             // learned push: its fixes, which an undo may free again
         double *l = nullptr, *u = nullptr;  // learned push: the original bounds an undo restores
-        int n0 = 0, nnz0 = 0, red_blocks_n0 = 1, udeg_at0 = 0;
+        int n0 = 0, nnz0 = 0, red_blocks_n0 = 1, udeg_at0 = 0, longest_col0 = 0, longest_row0 = 0,
+            beside0 = 0;
         int8_t *lfix0 = nullptr;
         double *l0 = nullptr, *u0 = nullptr;
         int *tp0 = nullptr, *ti0 = nullptr, *rp0 = nullptr, *ci0 = nullptr;
@@ -363,8 +366,10 @@ hipError_t exact_product(pdhg_solver *s, bool transpose, const double *vec, doub
 // mixed precision: chc = ch - E' y_a, bhc = bh - E x_a at the current anchor
 // (a no-op in float64 mode, where chc and bhc are ch and bh)
 hipError_t defect_refresh(pdhg_solver *s);
-// udeg_at: the common entry count of every column (1..3) of the current model, or 0
-hipError_t detect_uniform_columns(pdhg_solver *s);
+// udeg_at (the common entry count of every column, 1..3, or 0), longest_col,
+// longest_row and beside of the current model
+hipError_t row_shapes(pdhg_solver *s);
+bool uses_waves(const pdhg_solver *s, int kern, bool dual); // the tiles of `kern` run as waves
 // the primal half runs the uniform-column kernel: columns of 1-3 entries each,
 // 256-row tiles chosen by the library (an explicit lanes_at keeps the tiles)
 inline bool uses_uniform_kernel(const pdhg_solver *s)

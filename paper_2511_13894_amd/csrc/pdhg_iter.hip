@@ -215,6 +215,58 @@ __device__ __forceinline__ double row_block_sum(int beg, int end, const int *__r
     return q[0];
 }
 
+// Whether the tiles of `kern` run as waves (wave_row_sum; the same bits).
+// A wave's lanes go straight from index to operand to sum, where a tile's
+// products pass through LDS behind two barriers, so a wave is done sooner; a
+// tile reads its entries in fewer and fuller requests.  Hence waves where the
+// launch's waves are resident all at once (28 a CU at these kernels'
+// registers) and latency is what is left, and tiles beyond.  us per
+// iteration, tiles -> waves, fp64 (mixed): both halves of planted LPs (4-8
+// entries a column) with 4,000 columns 6.39 -> 5.52 (7.04 -> 5.70), 100,000
+// columns 13.6 -> 12.9 (13.3 -> 12.2); the dual half of power-law LPs with
+// 20,000 columns 7.97 -> 7.45 (8.29 -> 7.64), 200,000 columns (6,250 waves)
+// 23.4 -> 22.9 (21.1 -> 20.5); past the line, 120,000 planted rows (7,500
+// waves) 30.0 -> 30.5 (28.9 -> 28.8), 400,000 (25,000) 118.6 -> 119.2 (84.7
+// -> 89.9).  A row of many more entries than lanes is a chain the wave's other
+// lanes wait for: power-law columns of up to 200 entries stay in tiles (7.97
+// against 8.16 as waves).  Rows that gather next to the row before them (the
+// coupling rows of a multicommodity network, one column per commodity) share
+// gathered lines when more rows than entries sit in one load: with a quarter
+// of the entries in such rows waves win again once the launch is far past one
+// generation (256,000 rows 42.6 -> 40.2 (39.0 -> 34.1), 400,000 rows 63.6 ->
+// 60.0 (58.5 -> 50.3); 128,000 rows, 8,000 waves: 24.8 -> 25.4 (22.6 -> 22.9)).
+bool uses_waves(const pdhg_solver *s, int kern, bool dual)
+{
+    if (kern != -32 && kern != -64 && kern != -128 && kern != -256) return false;
+    const int G = kWaveTile / -kern;
+    if ((dual ? s->longest_row : s->longest_col) > kWaveTerms * G) return false;
+    const int64_t waves = ((int64_t)(dual ? s->m : s->n) * G + 63) / 64;
+    return waves <= kWavesResident || (dual && waves >= 2 * kWavesResident && 4 * (int64_t)s->beside >= s->nnz);
+}
+
+// --------------------------------------------- short rows, one wave each ---
+// The rows of one wave: 64/G rows of the 256/G-row tile that holds them
+// (wave_row_sum).  Lanes past the last row repeat it with no entries.
+template <int G>
+struct WaveRows {
+    int row, sub, beg, end;
+    bool mine;
+    TileRange tile;
+    __device__ __forceinline__ WaveRows(int rows_total, const int *__restrict__ ptr)
+    {
+        constexpr int R = 64 / G, T = kWaveTile / G;
+        const int r0 = xcd_block(blockIdx.x, gridDim.x) * R;
+        const int t0 = r0 / T * T;
+        const int r = r0 + (int)threadIdx.x / G;
+        mine = r < rows_total;
+        row = mine ? r : rows_total - 1;
+        sub = threadIdx.x % G;
+        end = ptr[row + 1];
+        beg = mine ? ptr[row] : end;
+        tile = tile_range(ptr, t0, rows_total - t0 < T ? rows_total - t0 : T);
+    }
+};
+
 // ---------------------------------------------------- check products ---
 // A check's products use the structure of the iteration kernel of the same
 // half (LDS tiles, one row per workgroup, or lane groups): they cost what an
@@ -234,6 +286,17 @@ __global__ __launch_bounds__(NT) void k_spmv_tiled(int rows_total, const int *__
     if ((int)threadIdx.x < rows) out[r0 + threadIdx.x] = s_sum[threadIdx.x];
 }
 
+template <typename VM, typename VV, int G>
+__global__ __launch_bounds__(64) void k_spmv_wave(int rows_total, const int *__restrict__ ptr, const int *__restrict__ idx,
+                                                 const VM *__restrict__ val, const VV *__restrict__ vec,
+                                                 double *__restrict__ out)
+{
+    __shared__ double s_prod[kWaveChunk];
+    const WaveRows<G> w(rows_total, ptr);
+    const double acc = wave_row_sum<G, VM, VV>(w.tile, w.beg, w.end, w.sub, idx, val, vec, s_prod);
+    if (w.sub == 0 && w.mine) out[w.row] = acc;
+}
+
 template <typename VM, typename VV>
 __global__ __launch_bounds__(kBlock) void k_spmv_rowblock(const int *__restrict__ ptr, const int *__restrict__ idx,
                                                          const VM *__restrict__ val, const VV *__restrict__ vec,
@@ -244,9 +307,10 @@ __global__ __launch_bounds__(kBlock) void k_spmv_rowblock(const int *__restrict_
     if (threadIdx.x == 0) out[r] = h;
 }
 
-// out = M vec (float64) with the kernel structure `kern` (lanes_* encoding)
+// out = M vec (float64) with the kernel structure `kern` (lanes_* encoding),
+// its tiles' sums by waves if `waves` (the same bits)
 template <typename VM, typename VV>
-static void check_spmv(hipStream_t st, int kern, int rows, const int *ptr, const int *idx, const VM *val,
+static void check_spmv(hipStream_t st, int kern, bool waves, int rows, const int *ptr, const int *idx, const VM *val,
                        const VV *vec, double *out)
 {
     if (rows <= 0) return;
@@ -259,6 +323,22 @@ static void check_spmv(hipStream_t st, int kern, int rows, const int *ptr, const
         return;
     }
     const int T = -kern;
+    if (waves) {
+#define PDHG_W_CASE(TT, GG)                                                                                      \
+    case TT:                                                                                                     \
+        hipLaunchKernelGGL((k_spmv_wave<VM, VV, GG>), dim3((rows + 64 / GG - 1) / (64 / GG)), dim3(64), 0, st,   \
+                           rows, ptr, idx, val, vec, out);                                                       \
+        break;
+        switch (T) {
+            PDHG_W_CASE(32, 8)
+            PDHG_W_CASE(64, 4)
+            PDHG_W_CASE(128, 2)
+        default:
+            PDHG_W_CASE(256, 1)
+        }
+#undef PDHG_W_CASE
+        return;
+    }
     const int rows_per = T > 1000 ? T - 1000 : T;
     const int grid = (rows + rows_per - 1) / rows_per;
 #define PDHG_CS_CASE(TT, RR, NT)                                                                                 \
@@ -297,7 +377,15 @@ static void row_product(const pdhg_solver *s, const VM *val, const VV *vec, doub
                            s->ci, val, vec, out);
         return;
     }
-    check_spmv<VM, VV>(s->stream, s->kern_a == kSell ? s->lanes_a : s->kern_a, s->m, s->rp, s->ci, val, vec, out);
+    check_spmv<VM, VV>(s->stream, s->kern_a == kSell ? s->lanes_a : s->kern_a, uses_waves(s, s->kern_a, true),
+                       s->m, s->rp, s->ci, val, vec, out);
+}
+
+// out = M vec for a matrix with the transpose's rows, in the primal half's structure
+template <typename VM, typename VV>
+static void col_product(const pdhg_solver *s, const VM *val, const VV *vec, double *out)
+{
+    check_spmv<VM, VV>(s->stream, s->kern_at, uses_waves(s, s->kern_at, false), s->n, s->tp, s->ti, val, vec, out);
 }
 
 hipError_t solver_product(pdhg_solver *s, bool transpose, const double *vec, double *out);
@@ -308,7 +396,7 @@ hipError_t exact_product(pdhg_solver *s, bool transpose, const double *vec, doub
     if (e != hipSuccess || !s->aerr) return e;
     hipStream_t st = s->stream;
     if (transpose) { // ety is free outside a check cycle
-        check_spmv<float, double>(st, s->kern_at, s->n, s->tp, s->ti, (const float *)s->aerr_t, vec, s->ety);
+        col_product<float, double>(s, (const float *)s->aerr_t, vec, s->ety);
         hipLaunchKernelGGL(k_add_to, dim3(grid_for(s->n, kBlock, 8192)), dim3(kBlock), 0, st, (int64_t)s->n, out,
                            (const double *)s->ety);
     } else {
@@ -322,8 +410,8 @@ hipError_t exact_product(pdhg_solver *s, bool transpose, const double *vec, doub
 hipError_t solver_product(pdhg_solver *s, bool transpose, const double *vec, double *out)
 {
     if (transpose) {
-        if (s->fp32) check_spmv<float, double>(s->stream, s->kern_at, s->n, s->tp, s->ti, (const float *)s->ahat_t, vec, out);
-        else check_spmv<double, double>(s->stream, s->kern_at, s->n, s->tp, s->ti, (const double *)s->ahat_t, vec, out);
+        if (s->fp32) col_product<float, double>(s, (const float *)s->ahat_t, vec, out);
+        else col_product<double, double>(s, (const double *)s->ahat_t, vec, out);
     } else if (s->kern_a == kSell) {
         sell_product(s, vec, out);
     } else {
@@ -441,6 +529,48 @@ __global__ __launch_bounds__(NT) void k_dual_tiled(int m, const int *__restrict_
     dual_update(r, s_sum[tid], yr, br, ar, sn, y, yp, sc, store_cand);
 }
 
+template <typename V, int G>
+__global__ __launch_bounds__(64) void k_primal_wave(int n, const int *__restrict__ tp, const int *__restrict__ ti,
+                                                   const V *__restrict__ atv, const double *__restrict__ y,
+                                                   const double *__restrict__ ch, const V *__restrict__ lh,
+                                                   const V *__restrict__ uh, V *__restrict__ x,
+                                                   const double *__restrict__ xa, V *__restrict__ xbar,
+                                                   double *__restrict__ xp, const DevState *__restrict__ st, int i,
+                                                   int store_cand)
+{
+    __shared__ double s_prod[kWaveChunk];
+    const int done = st->done;
+    const WaveRows<G> w(n, tp);
+    const int j = w.row;
+    const double aj = xa[j], xj = iterate_value<V>(x[j], aj), cj = ch[j], lo = (double)lh[j], hi = (double)uh[j];
+    if (done) return;
+    const StepScalars sc = step_scalars(st, i);
+    const double acc = wave_row_sum<G, V, double>(w.tile, w.beg, w.end, w.sub, ti, atv, y, s_prod);
+    if (w.sub != 0 || !w.mine) return;
+    primal_update<V>(j, acc, xj, cj, lo, hi, aj, x, xbar, xp, sc, store_cand);
+}
+
+template <typename V, int G>
+__global__ __launch_bounds__(64) void k_dual_wave(int m, const int *__restrict__ rp, const int *__restrict__ ci,
+                                                 const V *__restrict__ av, const V *__restrict__ xbar,
+                                                 const double *__restrict__ bh, const int8_t *__restrict__ sense,
+                                                 double *__restrict__ y, const double *__restrict__ ya,
+                                                 double *__restrict__ yp, const DevState *__restrict__ st, int i,
+                                                 int store_cand)
+{
+    __shared__ double s_prod[kWaveChunk];
+    const int done = st->done;
+    const WaveRows<G> w(m, rp);
+    const int r = w.row;
+    const double yr = y[r], br = bh[r], ar = ya[r];
+    const int8_t sn = sense[r];
+    if (done) return;
+    const StepScalars sc = step_scalars(st, i);
+    const double acc = wave_row_sum<G, V, V>(w.tile, w.beg, w.end, w.sub, ci, av, xbar, s_prod);
+    if (w.sub != 0 || !w.mine) return;
+    dual_update(r, acc, yr, br, ar, sn, y, yp, sc, store_cand);
+}
+
 // Primal half when every column of A has the same D <= 3 entries (every
 // transpose row starts at j*D: network and transportation LPs, and their
 // push models on the free columns): one thread per column, with no
@@ -511,6 +641,24 @@ static void launch_primal(pdhg_solver *s, int i, int store, hipEvent_t e0 = null
                     (V *)s->x, (const double *)s->xa, (V *)s->xbar, (double *)s->xp, s->st, i, store);
         return;
     }
+    if (L < 0 && uses_waves(s, L, false)) {
+#define PDHG_W_CASE(TT, GG)                                                                                      \
+    case TT:                                                                                                     \
+        PDHG_LAUNCH(e0, e1, (k_primal_wave<V, GG>), dim3((s->n + 64 / GG - 1) / (64 / GG)), dim3(64), s->stream, \
+                    s->n, s->tp, s->ti, (const V *)s->ahat_t, (const double *)s->y, s->chc, (const V *)s->lh,   \
+                    (const V *)s->uh, (V *)s->x, (const double *)s->xa, (V *)s->xbar, (double *)s->xp, s->st, i, \
+                    store);                                                                                      \
+        break;
+        switch (-L) {
+            PDHG_W_CASE(32, 8)
+            PDHG_W_CASE(64, 4)
+            PDHG_W_CASE(128, 2)
+        default:
+            PDHG_W_CASE(256, 1)
+        }
+#undef PDHG_W_CASE
+        return;
+    }
     if (L < 0) { // LDS-tiled kernel: -T (256 threads) or -(1000 + T) (64 threads)
         const int T = -L;
         const int rows_per = T > 1000 ? T - 1000 : T;
@@ -575,6 +723,23 @@ static void launch_dual(pdhg_solver *s, int i, int store, hipEvent_t e0 = nullpt
         PDHG_LAUNCH(e0, e1, (k_dual_rowblock<V>), dim3(s->m), dim3(kBlock), s->stream, s->m, s->rp, s->ci,
                     (const V *)s->ahat, (const V *)s->xbar, (const double *)s->bhc, s->sense, (double *)s->y,
                     (const double *)s->ya, (double *)s->yp, s->st, i, store);
+        return;
+    }
+    if (L < 0 && uses_waves(s, L, true)) {
+#define PDHG_W_CASE(TT, GG)                                                                                      \
+    case TT:                                                                                                     \
+        PDHG_LAUNCH(e0, e1, (k_dual_wave<V, GG>), dim3((s->m + 64 / GG - 1) / (64 / GG)), dim3(64), s->stream,   \
+                    s->m, s->rp, s->ci, (const V *)s->ahat, (const V *)s->xbar, (const double *)s->bhc, s->sense, \
+                    (double *)s->y, (const double *)s->ya, (double *)s->yp, s->st, i, store);                   \
+        break;
+        switch (-L) {
+            PDHG_W_CASE(32, 8)
+            PDHG_W_CASE(64, 4)
+            PDHG_W_CASE(128, 2)
+        default:
+            PDHG_W_CASE(256, 1)
+        }
+#undef PDHG_W_CASE
         return;
     }
     if (L < 0) {
@@ -788,10 +953,10 @@ static void check_impl(pdhg_solver *s, const double *xc, const double *yc, doubl
     hipStream_t st = s->stream;
     if (s->kern_a == kSell) sell_product(s, xc, s->ax);
     else row_product<V, double>(s, (const V *)s->ahat, xc, s->ax);
-    check_spmv<V, double>(st, s->kern_at, s->n, s->tp, s->ti, (const V *)s->ahat_t, yc, s->aty);
+    col_product<V, double>(s, (const V *)s->ahat_t, yc, s->aty);
     if (s->aerr) { // mixed mode: the float64 products are these plus E xc and E' yc
         row_product<float, double>(s, (const float *)s->aerr, xc, s->ex);
-        check_spmv<float, double>(st, s->kern_at, s->n, s->tp, s->ti, (const float *)s->aerr_t, yc, s->ety);
+        col_product<float, double>(s, (const float *)s->aerr_t, yc, s->ety);
     }
     const int gm = s->red_blocks_m, gn = s->red_blocks_n;
     hipLaunchKernelGGL(k_check_rows, dim3(gm), dim3(kBlock), 0, st, s->m, s->ax, (const double *)(s->aerr ? s->ex : nullptr),
@@ -840,34 +1005,57 @@ hipError_t launch_check(pdhg_solver *s, int mode, int len)
     return hipGetLastError();
 }
 
-// bad |= 1 if some row of `ptr` (rows + 1 entries) does not hold exactly D entries
-__global__ __launch_bounds__(kBlock) void k_uniform_rows(int rows, const int *__restrict__ ptr, int D,
-                                                        unsigned *__restrict__ bad)
+// out = {1 if a column does not hold exactly D entries, longest column,
+// longest row, entries of the rows of more than G entries whose first column
+// lies at most kBeside after the first one of the row before}
+constexpr int kBeside = 4;
+
+__global__ __launch_bounds__(kBlock) void k_row_shapes(int n, const int *__restrict__ tp, int D, int m,
+                                                      const int *__restrict__ rp, const int *__restrict__ ci, int G,
+                                                      int *__restrict__ out)
 {
-    for (int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x; r <= rows; r += (int64_t)gridDim.x * kBlock)
-        if (ptr[r] != (int)(r * D)) {
-            atomicOr(bad, 1u);
-            return;
-        }
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x, step = (int64_t)gridDim.x * kBlock;
+    for (int64_t j = t; j < n; j += step) {
+        const int len = tp[j + 1] - tp[j];
+        if (len != D) v[0] = 1.0;
+        v[1] = fmax(v[1], (double)len);
+    }
+    for (int64_t r = t; r < m; r += step) {
+        const int b = rp[r], len = rp[r + 1] - b;
+        v[2] = fmax(v[2], (double)len);
+        const int a = r > 0 ? rp[r - 1] : b;
+        if (len <= G || a == b) continue; // a < b: the row before has a first entry
+        const int d = ci[b] - ci[a];
+        if (d > 0 && d <= kBeside) v[3] += len;
+    }
+    block_reduce<4>(v, 7u);
+    if (threadIdx.x != 0) return;
+    for (int q = 0; q < 3; q++)
+        if (v[q] > 0.0) atomicMax(out + q, (int)v[q]);
+    if (v[3] > 0.0) atomicAdd(out + 3, (int)v[3]);
 }
 
-__global__ void k_zero_u32(unsigned *p) { *p = 0u; }
+__global__ void k_zero_shapes(int *p) { p[threadIdx.x] = 0; }
 
-hipError_t detect_uniform_columns(pdhg_solver *s)
+hipError_t row_shapes(pdhg_solver *s)
 {
-    s->udeg_at = 0;
-    if (s->n <= 0 || s->nnz % s->n != 0) return hipSuccess;
-    const int D = s->nnz / s->n;
-    if (D < 1 || D > 3) return hipSuccess;
-    unsigned *d_bad = (unsigned *)s->redout; // small scratch of the handle, free outside a check
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, s->stream, d_bad);
-    hipLaunchKernelGGL(k_uniform_rows, dim3(grid_for((int64_t)s->n + 1, kBlock, 4096)), dim3(kBlock), 0, s->stream,
-                       s->n, s->tp, D, d_bad);
-    unsigned bad = 1;
-    hipError_t e = hipMemcpyAsync(&bad, d_bad, sizeof(unsigned), hipMemcpyDeviceToHost, s->stream);
+    s->udeg_at = s->longest_col = s->longest_row = s->beside = 0;
+    if (s->n <= 0 || s->m <= 0) return hipSuccess;
+    const int D = s->nnz % s->n == 0 ? s->nnz / s->n : 0;
+    const int G = s->kern_a < 0 && s->kern_a >= -kWaveTile ? kWaveTile / -s->kern_a : 64;
+    int *d = (int *)s->redout, h[4] = {1, 0, 0, 0}; // small scratch of the handle, free outside a check
+    hipLaunchKernelGGL(k_zero_shapes, dim3(1), dim3(4), 0, s->stream, d);
+    hipLaunchKernelGGL(k_row_shapes, dim3(grid_for((int64_t)std::max(s->n, s->m), kBlock, 1024)), dim3(kBlock), 0,
+                       s->stream, s->n, s->tp, D, s->m, s->rp, s->ci, G, d);
+    hipError_t e = hipMemcpyAsync(h, d, sizeof h, hipMemcpyDeviceToHost, s->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
-    if (e == hipSuccess && bad == 0) s->udeg_at = D;
-    return e;
+    if (e != hipSuccess) return e;
+    if (h[0] == 0 && D >= 1 && D <= 3) s->udeg_at = D;
+    s->longest_col = h[1];
+    s->longest_row = h[2];
+    s->beside = h[3];
+    return hipSuccess;
 }
 
 hipError_t defect_refresh(pdhg_solver *s)
@@ -883,7 +1071,7 @@ hipError_t defect_refresh(pdhg_solver *s)
     if (s->kern_a == kSell) sell_product(s, xa, s->bhc);
     else row_product<float, double>(s, (const float *)s->ahat, xa, s->bhc);
     row_product<float, double>(s, (const float *)s->aerr, xa, s->ex);
-    check_spmv<float, double>(st, s->kern_at, s->n, s->tp, s->ti, (const float *)s->aerr_t, ya, s->ety);
+    col_product<float, double>(s, (const float *)s->aerr_t, ya, s->ety);
     const int g = grid_for((int64_t)s->n + s->m, kBlock, 8192);
     hipLaunchKernelGGL(k_defect_set, dim3(g), dim3(kBlock), 0, st, s->n, s->m, s->st, 1, s->ch,
                        (const double *)s->ety, (const double *)nullptr, s->chc, (const double *)s->bh,

@@ -233,6 +233,109 @@ __device__ __forceinline__ void tile_row_sums(TileRange range, int r0, int rows,
     __syncthreads();
 }
 
+// --------------------------------------------- short rows, one wave each ---
+// The sums of a tile of T = 256/G rows (tile_row_sums with 256 threads), bit
+// for bit, without a workgroup: a wave takes 64/G rows of the tile, G lanes a
+// row.  A lane loads its row's entries sub, sub+G, ... itself, all of them at
+// once (two, four or eight, by the longest row of the wave), and adds their
+// rounded products in the tile's order: nothing passes through LDS and no
+// barrier waits for the slowest of four waves.  A wave with a row of more than
+// eight entries a lane, or in a tile of more than one chunk, streams its
+// entries through LDS as the tile does, in pieces of kWaveChunk, with the
+// tile's restart of the lanes' order at each chunk (uses_waves: where, and the
+// figures).
+constexpr int kWaveTile = 256;   // threads of the tile whose sums a wave repeats
+constexpr int kWaveChunk = 512;  // entries of a wave's rows in LDS at once
+constexpr int kWaveTerms = 16;   // longest row a lane group takes, in entries per lane
+constexpr int kWavesResident = 256 * 28; // waves the chip holds at once (uses_waves)
+
+template <int G, int U, typename VM, typename VV>
+__device__ __forceinline__ double group_terms(int beg, int end, int sub, const int *__restrict__ idx,
+                                              const VM *__restrict__ val, const VV *__restrict__ vec)
+{
+#pragma clang fp contract(off)
+    const int e = beg + sub, last = end - 1;
+    double acc = 0.0;
+    if (e < end) {
+        int id[U];
+        VM v[U];
+        VV g[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int k = e + u * G < last ? e + u * G : last;
+            id[u] = idx[k];
+            v[u] = val[k];
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++) g[u] = vec[id[u]];
+        acc += (double)v[0] * (double)g[0];
+#pragma unroll
+        for (int u = 1; u < U; u++)
+            if (e + u * G < end) acc += (double)v[u] * (double)g[u];
+    }
+    return acc;
+}
+
+template <int G, typename VM, typename VV>
+__device__ __forceinline__ double wave_row_sum(TileRange tile, int beg, int end, int sub, const int *__restrict__ idx,
+                                               const VM *__restrict__ val, const VV *__restrict__ vec,
+                                               double *s_prod)
+{
+    constexpr int C = kTileU * kWaveTile;
+    const int len = end - beg;
+    double acc = 0.0;
+    if (tile.end - tile.beg <= C && !__builtin_amdgcn_ballot_w64(len > 8 * G)) {
+        if (__builtin_amdgcn_ballot_w64(len > 4 * G)) acc = group_terms<G, 8>(beg, end, sub, idx, val, vec);
+        else if (__builtin_amdgcn_ballot_w64(len > 2 * G)) acc = group_terms<G, 4>(beg, end, sub, idx, val, vec);
+        else acc = group_terms<G, 2>(beg, end, sub, idx, val, vec);
+        return group_sum<G>(acc);
+    }
+    const int lane = threadIdx.x;
+    const int wb = __builtin_amdgcn_readfirstlane(beg), we = __builtin_amdgcn_readlane(end, 63);
+    for (int cs = tile.beg; cs < tile.end; cs += C) {
+        const int ce = cs + C < tile.end ? cs + C : tile.end;
+        const int ca = wb > cs ? wb : cs, cb = we < ce ? we : ce; // the wave's entries of the chunk
+        const int hi = end < ce ? end : ce;
+        int q = (beg > cs ? beg : cs) + sub;
+        for (int ss = ca; ss < cb; ss += kWaveChunk) {
+            const int se = ss + kWaveChunk < cb ? ss + kWaveChunk : cb;
+            int id[kTileU];
+            double v[kTileU], g[kTileU];
+#pragma unroll
+            for (int u = 0; u < kTileU; u++) {
+                id[u] = 0;
+                v[u] = 0.0;
+                if (ss + u * 64 < se) {
+                    const int k = ss + lane + u * 64;
+                    const int kc = k < se ? k : se - 1;
+                    id[u] = idx[kc];
+                    v[u] = (double)val[kc];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kTileU; u++) g[u] = ss + u * 64 < se ? (double)vec[id[u]] : 0.0;
+#pragma unroll
+            for (int u = 0; u < kTileU; u++) {
+                const int k = ss + lane + u * 64;
+                if (k < se) s_prod[k - ss] = v[u] * g[u];
+            }
+            __syncthreads();
+            const int h = hi < se ? hi : se;
+            for (; q + 3 * G < h; q += 4 * G) {
+                const double p0 = s_prod[q - ss], p1 = s_prod[q + G - ss];
+                const double p2 = s_prod[q + 2 * G - ss], p3 = s_prod[q + 3 * G - ss];
+                acc += p0;
+                acc += p1;
+                acc += p2;
+                acc += p3;
+            }
+            for (; q < h; q += G) acc += s_prod[q - ss];
+            __syncthreads();
+        }
+    }
+    return group_sum<G>(acc);
+}
+
 // The check's quantities from per-block (or per-tile) partials: slot q folds
 // its partials lo..hi-1 (row slots from pm + q*sm over [m0, m1), column slots
 // from pn + q*sn over [n0, n1)), thread t taking lo+t, lo+t+kBlock, ... in

@@ -642,15 +642,12 @@ __global__ __launch_bounds__(kResThreads) void k_resident_power(ResMatrix<V> a, 
 }
 
 // ------------------------------------------------------------------- plan ---
-// out[0] = longest column, out[1 + k] = longest row of segment k
-__global__ __launch_bounds__(kBlock) void k_longest(int n, const int *__restrict__ tp, RowSegs sg,
-                                                   const int *__restrict__ rp, int *__restrict__ out)
+// out[k] = longest row of segment k
+__global__ __launch_bounds__(kBlock) void k_longest(RowSegs sg, const int *__restrict__ rp, int *__restrict__ out)
 {
-    const int k = blockIdx.x; // 0: the columns, else segment k - 1
-    const int r0 = k == 0 ? 0 : sg.row0[k - 1], r1 = k == 0 ? n : sg.row0[k];
-    const int *ptr = k == 0 ? tp : rp;
+    const int k = blockIdx.x;
     double v[1] = {0.0};
-    for (int r = r0 + threadIdx.x; r < r1; r += kBlock) v[0] = fmax(v[0], (double)(ptr[r + 1] - ptr[r]));
+    for (int r = sg.row0[k] + threadIdx.x; r < sg.row0[k + 1]; r += kBlock) v[0] = fmax(v[0], (double)(rp[r + 1] - rp[r]));
     block_reduce<1>(v, 1u);
     if (threadIdx.x == 0) out[k] = (int)v[0];
 }
@@ -701,11 +698,14 @@ hipError_t resident_plan(pdhg_solver *s)
             rd.slots[q] = k; // the segment, until its longest row is known
         }
     }
-    int *out = (int *)s->redout, longest[1 + kMaxSegs] = {}; // small scratch of the handle, free outside a check
-    hipLaunchKernelGGL(k_longest, dim3(1 + sg.count), dim3(kBlock), 0, s->stream, s->n, s->tp, sg, s->rp, out);
-    hipError_t e = hipMemcpyAsync(longest, out, sizeof(int) * (1 + (size_t)sg.count), hipMemcpyDeviceToHost, s->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
-    if (e != hipSuccess) return e;
+    int longest[1 + kMaxSegs] = {s->longest_col, s->longest_row};
+    if (segs) { // per segment
+        int *out = (int *)s->redout; // small scratch of the handle, free outside a check
+        hipLaunchKernelGGL(k_longest, dim3(sg.count), dim3(kBlock), 0, s->stream, sg, s->rp, out);
+        hipError_t e = hipMemcpyAsync(longest + 1, out, sizeof(int) * (size_t)sg.count, hipMemcpyDeviceToHost, s->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
+        if (e != hipSuccess) return e;
+    }
     int slots = 0;
     for (int q = 0; q < rd.count; q++) {
         rd.slots[q] = (longest[1 + rd.slots[q]] + (1 << rd.hs[q]) - 1) >> rd.hs[q];
