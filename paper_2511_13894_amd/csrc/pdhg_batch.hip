@@ -85,10 +85,110 @@ __global__ __launch_bounds__(NT) void kb_dual(const int4 *__restrict__ tiles, co
     dual_update(r, s_sum[tid], yr, br, ar, sn, y, yp, sc, store_cand);
 }
 
+// The rows of one wave: 64/G rows of the tile of 256/G rows blockIdx.x / 4
+// (wave_row_sum).  Lanes past the tile's last row repeat it with no entries.
+constexpr int kTileWaves = 4;
+
+template <int G>
+struct TileWave {
+    int lp, row, sub;
+    bool any, mine; // the wave, the lane has a row
+    TileRange tile;
+    __device__ __forceinline__ TileWave(const int4 *__restrict__ tiles, const int *__restrict__ ptr)
+    {
+        const int b = xcd_range_block(blockIdx.x, gridDim.x);
+        const int4 tl = tiles[b / kTileWaves];
+        const int k = b % kTileWaves * (64 / G) + (int)threadIdx.x / G;
+        lp = tl.x;
+        any = b % kTileWaves * (64 / G) < tl.z;
+        mine = k < tl.z;
+        row = tl.y + (mine ? k : tl.z - 1);
+        sub = threadIdx.x % G;
+        tile = tile_range(ptr, tl.y, tl.z);
+    }
+};
+
+template <typename V, int G>
+__global__ __launch_bounds__(64) void kb_primal_wave(const int4 *__restrict__ tiles, const int *__restrict__ tp,
+                                                    const int *__restrict__ ti, const V *__restrict__ atv,
+                                                    const double *__restrict__ y, const double *__restrict__ ch,
+                                                    const V *__restrict__ lh, const V *__restrict__ uh,
+                                                    V *__restrict__ x, const double *__restrict__ xa,
+                                                    V *__restrict__ xbar, double *__restrict__ xp,
+                                                    const DevState *__restrict__ sts, int i, int store_cand)
+{
+    __shared__ double s_prod[kWaveChunk];
+    const TileWave<G> w(tiles, tp);
+    const DevState *st = sts + w.lp;
+    if (!w.any || st->done) return;
+    const int j = w.row;
+    const int end = tp[j + 1], beg = w.mine ? tp[j] : end;
+    const double aj = xa[j], xj = iterate_value<V>(x[j], aj), cj = ch[j], lo = (double)lh[j], hi = (double)uh[j];
+    const StepScalars sc = step_scalars(st, i);
+    const double acc = wave_row_sum<G, V, double>(w.tile, beg, end, w.sub, ti, atv, y, s_prod);
+    if (w.sub != 0 || !w.mine) return;
+    primal_update<V>(j, acc, xj, cj, lo, hi, aj, x, xbar, xp, sc, store_cand);
+}
+
+template <typename V, int G>
+__global__ __launch_bounds__(64) void kb_dual_wave(const int4 *__restrict__ tiles, const int *__restrict__ rp,
+                                                  const int *__restrict__ ci, const V *__restrict__ av,
+                                                  const V *__restrict__ xbar, const double *__restrict__ bh,
+                                                  const int8_t *__restrict__ sense, double *__restrict__ y,
+                                                  const double *__restrict__ ya, double *__restrict__ yp,
+                                                  const DevState *__restrict__ sts, int i, int store_cand)
+{
+    __shared__ double s_prod[kWaveChunk];
+    const TileWave<G> w(tiles, rp);
+    const DevState *st = sts + w.lp;
+    if (!w.any || st->done) return;
+    const int r = w.row;
+    const int end = rp[r + 1], beg = w.mine ? rp[r] : end;
+    const double yr = y[r], br = bh[r], ar = ya[r];
+    const int8_t sn = sense[r];
+    const StepScalars sc = step_scalars(st, i);
+    const double acc = wave_row_sum<G, V, V>(w.tile, beg, end, w.sub, ci, av, xbar, s_prod);
+    if (w.sub != 0 || !w.mine) return;
+    dual_update(r, acc, yr, br, ar, sn, y, yp, sc, store_cand);
+}
+
+// Whether a launch over `tiles` tiles runs them as waves (uses_waves: why; the
+// same sums).  The tile lists shrink as LPs stop, and the launches follow.  The
+// line lies at half the waves the chip holds: solve of 64 LPs of 500-5,000
+// rows, most of them stopped after a quarter of its iterations, 12.75 -> 12.30
+// us per iteration; 16 LPs of 100-400 rows 8.0 -> 7.2 us in the solve, 6.94 ->
+// 6.14 in the push; with the line at all the waves the push of 64 LPs of up
+// to 20,000 rows 17.2 -> 18.0 us, with no line that of 500-5,000 rows 17.0 ->
+// 19.5 (the LPs gather from short vectors, so tiles wait less).
+static bool batch_waves(const pdhg_batch *b, int kern, int tiles, bool dual)
+{
+    if (kern != -32 && kern != -64 && kern != -128 && kern != -256) return false;
+    if ((dual ? b->s->longest_row : b->s->longest_col) > kWaveTerms * (kWaveTile / -kern)) return false;
+    return kTileWaves * (int64_t)tiles <= kWavesResident / 2;
+}
+
 template <typename V>
 static void launch_primal_b(pdhg_batch *b, int i, int store, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr)
 {
     pdhg_solver *s = b->s;
+    if (batch_waves(b, b->kern_at, b->n_ptiles, false)) {
+#define PDHG_W_CASE(TT, GG)                                                                                      \
+    case TT:                                                                                                     \
+        PDHG_LAUNCH(e0, e1, (kb_primal_wave<V, GG>), dim3(kTileWaves * b->n_ptiles), dim3(64), s->stream,            \
+                    b->ptiles, s->tp, s->ti, (const V *)s->ahat_t, (const double *)s->y, s->chc,                 \
+                    (const V *)s->lh, (const V *)s->uh, (V *)s->x, (const double *)s->xa, (V *)s->xbar,          \
+                    (double *)s->xp, b->sts, i, store);                                                          \
+        break;
+        switch (-b->kern_at) {
+            PDHG_W_CASE(32, 8)
+            PDHG_W_CASE(64, 4)
+            PDHG_W_CASE(128, 2)
+        default:
+            PDHG_W_CASE(256, 1)
+        }
+#undef PDHG_W_CASE
+        return;
+    }
 #define PDHG_BP_CASE(TT, RR, NT)                                                                               \
     case TT:                                                                                                   \
         PDHG_LAUNCH(e0, e1, (kb_primal<V, RR, NT>), dim3(b->n_ptiles), dim3(NT), s->stream, b->ptiles, s->tp, \
@@ -112,6 +212,24 @@ template <typename V>
 static void launch_dual_b(pdhg_batch *b, int i, int store, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr)
 {
     pdhg_solver *s = b->s;
+    if (batch_waves(b, b->kern_a, b->n_dtiles, true)) {
+#define PDHG_W_CASE(TT, GG)                                                                                      \
+    case TT:                                                                                                     \
+        PDHG_LAUNCH(e0, e1, (kb_dual_wave<V, GG>), dim3(kTileWaves * b->n_dtiles), dim3(64), s->stream,            \
+                    b->dtiles, s->rp, s->ci, (const V *)s->ahat, (const V *)s->xbar,                             \
+                    (const double *)s->bhc, s->sense, (double *)s->y, (const double *)s->ya,                     \
+                    (double *)s->yp, b->sts, i, store);                                                          \
+        break;
+        switch (-b->kern_a) {
+            PDHG_W_CASE(32, 8)
+            PDHG_W_CASE(64, 4)
+            PDHG_W_CASE(128, 2)
+        default:
+            PDHG_W_CASE(256, 1)
+        }
+#undef PDHG_W_CASE
+        return;
+    }
 #define PDHG_BD_CASE(TT, RR, NT)                                                                               \
     case TT:                                                                                                   \
         PDHG_LAUNCH(e0, e1, (kb_dual<V, RR, NT>), dim3(b->n_dtiles), dim3(NT), s->stream, b->dtiles, s->rp,   \
@@ -319,12 +437,43 @@ __global__ __launch_bounds__(NT) void kb_spmv(const int4 *__restrict__ tiles, co
     if ((int)threadIdx.x < tl.z) out[tl.y + threadIdx.x] = s_sum[threadIdx.x];
 }
 
+template <typename VM, typename VV, int G>
+__global__ __launch_bounds__(64) void kb_spmv_wave(const int4 *__restrict__ tiles, const int *__restrict__ ptr,
+                                                  const int *__restrict__ idx, const VM *__restrict__ val,
+                                                  const VV *__restrict__ vec, double *__restrict__ out,
+                                                  const DevState *__restrict__ sts, const double *__restrict__ skip)
+{
+    __shared__ double s_prod[kWaveChunk];
+    const TileWave<G> w(tiles, ptr);
+    if (!w.any || (sts ? sts[w.lp].done != 0 : skip[w.lp] != 0.0)) return; // uniform over the wave
+    const int r = w.row;
+    const int end = ptr[r + 1], beg = w.mine ? ptr[r] : end;
+    const double acc = wave_row_sum<G, VM, VV>(w.tile, beg, end, w.sub, idx, val, vec, s_prod);
+    if (w.sub == 0 && w.mine) out[r] = acc;
+}
+
 template <typename VM, typename VV>
 static void launch_spmv_b(pdhg_batch *b, int kern, const int4 *tiles, int ntiles, const int *ptr, const int *idx,
                           const VM *val, const VV *vec, double *out, const double *skip = nullptr)
 {
     if (ntiles <= 0) return;
     hipStream_t st = b->s->stream;
+    if (batch_waves(b, kern, ntiles, tiles == b->dtiles)) {
+#define PDHG_W_CASE(TT, GG)                                                                                      \
+    case TT:                                                                                                     \
+        hipLaunchKernelGGL((kb_spmv_wave<VM, VV, GG>), dim3(kTileWaves * ntiles), dim3(64), 0, st, tiles, ptr,   \
+                           idx, val, vec, out, skip ? nullptr : b->sts, skip);                                   \
+        break;
+        switch (-kern) {
+            PDHG_W_CASE(32, 8)
+            PDHG_W_CASE(64, 4)
+            PDHG_W_CASE(128, 2)
+        default:
+            PDHG_W_CASE(256, 1)
+        }
+#undef PDHG_W_CASE
+        return;
+    }
 #define PDHG_BS_CASE(TT, RR, NT)                                                                               \
     case TT:                                                                                                   \
         hipLaunchKernelGGL((kb_spmv<VM, VV, RR, NT>), dim3(ntiles), dim3(NT), 0, st, tiles, ptr, idx, val, vec, \

@@ -47,3 +47,21 @@ def test_waves_follow_the_oracle(lanes, precision):
             o.iterate(1)
             for u, v in zip(g.get_iterate(), o.iterate_state()):
                 assert np.abs(u - v).max() <= tol * max(1.0, np.abs(v).max()), t
+
+
+@pytest.mark.parametrize("lanes", [-32, -64, -128, -256])
+def test_waves_in_a_batch_equal_the_lp_alone(lanes):
+    # the bounds of the other comparison of a batch with its LPs alone: their
+    # scaling adds the same terms in another order
+    lps = [_edges(lanes, False), lpgen.planted(150, 401, 9, deg=4, ineq_frac=0.5), _edges(lanes, True)]
+    for pick in ([0, 1], [2, 1], [1]):
+        kw = dict(lanes_at=lanes, lanes_a=lanes, max_iter=256, eps_rel=1e-12)
+        print(f"[waves] batch {lanes} {pick}", flush=True)
+        b = pdhg.Batch([lps[k] for k in pick], **kw)
+        res = b.solve()
+        for i, k in enumerate(pick):
+            g = pdhg.Solver(lps[k], **kw)
+            r = g.solve()
+            assert (r.iters, r.status) == (res[i].iters, res[i].status)
+            for u, v in zip(b.get_solution(i)[:2], g.get_solution()[:2]):
+                np.testing.assert_allclose(u, v, rtol=1e-9, atol=1e-12)
