@@ -591,26 +591,65 @@ __global__ __launch_bounds__(kBlock) void kb_sumsq(const int4 *__restrict__ tile
     if (threadIdx.x == 0) part[blockIdx.x] = q[0];
 }
 
-// per-LP power step (the single-LP rule): ps = {lambda[count], done[count],
-// steps[count]}; rho = u'u from the LP's row tiles, w'w from its column tiles
-__global__ __launch_bounds__(kBlock) void kb_power_finish(const int *__restrict__ rm_start,
-                                                         const double *__restrict__ pm,
-                                                         const int *__restrict__ rn_start,
-                                                         const double *__restrict__ pn, int count, double tol,
-                                                         double *__restrict__ ps)
+// Partial sums of squares of u over the row tiles and of w over the column
+// tiles of the LPs still iterating (the others' partials are not read).
+__global__ __launch_bounds__(kBlock) void kb_power_partials(const int4 *__restrict__ rm, int n_rm,
+                                                           const double *__restrict__ u, double *__restrict__ pm,
+                                                           const int4 *__restrict__ rn, const double *__restrict__ w,
+                                                           double *__restrict__ pn, const double *__restrict__ done)
 {
-    const int lp = blockIdx.x;
-    if (ps[count + lp] != 0.0) return;
+    const bool rows = (int)blockIdx.x < n_rm;
+    const int b = rows ? blockIdx.x : blockIdx.x - n_rm;
+    const int4 tl = rows ? rm[b] : rn[b];
+    if (done[tl.x] != 0.0) return;
+    double q[1] = {0.0};
+    if ((int)threadIdx.x < tl.z) {
+        const double a = (rows ? u : w)[tl.y + threadIdx.x];
+        q[0] = a * a;
+    }
+    block_reduce<1>(q, 0u);
+    if (threadIdx.x == 0) (rows ? pm : pn)[b] = q[0];
+}
+
+// A step's end on a column tile (the single-LP rule): its LP's rho = u'u from
+// the row tiles and w'w from the column tiles, in a fixed order by every tile
+// of the LP; the decision from them and the state before the step, old =
+// {lambda[count], done[count], steps[count]}; v = w / lambda unless the LP
+// stops.  The LP's first tile writes the state after the step (now, another
+// buffer: the LP's other tiles may still read old).
+__global__ __launch_bounds__(kBlock) void kb_power_end(const int4 *__restrict__ rn, const int *__restrict__ rm_start,
+                                                      const double *__restrict__ pm, const int *__restrict__ rn_start,
+                                                      const double *__restrict__ pn, int count, double tol,
+                                                      const double *__restrict__ old, double *__restrict__ now,
+                                                      const double *__restrict__ w, double *__restrict__ v)
+{
+    __shared__ double s_lam;
+    const int4 tl = rn[blockIdx.x];
+    const int lp = tl.x;
+    const bool first = (int)blockIdx.x == rn_start[lp];
+    if (old[count + lp] != 0.0) {
+        if (first && threadIdx.x < 3) now[threadIdx.x * count + lp] = old[threadIdx.x * count + lp];
+        return;
+    }
     double q[2] = {0.0, 0.0};
     for (int t = rm_start[lp] + threadIdx.x; t < rm_start[lp + 1]; t += kBlock) q[0] += pm[t];
     for (int t = rn_start[lp] + threadIdx.x; t < rn_start[lp + 1]; t += kBlock) q[1] += pn[t];
     block_reduce<2>(q, 0u);
     if (threadIdx.x == 0) {
         const double rho = q[0], ww = q[1], lam = sqrt(ww);
-        ps[lp] = lam;
-        ps[2 * count + lp] += 1.0;
-        if (power_stops(rho, ww, lam, tol)) ps[count + lp] = 1.0;
+        const bool stops = power_stops(rho, ww, lam, tol);
+        s_lam = stops ? 0.0 : lam;
+        if (first) {
+            now[lp] = lam;
+            now[count + lp] = stops ? 1.0 : 0.0;
+            now[2 * count + lp] = old[2 * count + lp] + 1.0;
+        }
     }
+    __syncthreads();
+    const double l = s_lam;
+    if (!(l > 0.0) || (int)threadIdx.x >= tl.z) return;
+    const int j = tl.y + threadIdx.x;
+    v[j] = w[j] / l;
 }
 
 // the power iteration's start on every column of an LP, numbered from the
@@ -642,16 +681,6 @@ __global__ __launch_bounds__(kBlock) void kb_div_start(const int4 *__restrict__ 
     if ((int)threadIdx.x >= tl.z) return;
     const int j = tl.y + threadIdx.x;
     v[j] = v[j] / ps[3 * count + tl.x];
-}
-
-__global__ __launch_bounds__(kBlock) void kb_normalize(const int4 *__restrict__ rn, const double *__restrict__ w,
-                                                      const double *__restrict__ ps, int count, double *__restrict__ v)
-{
-    const int4 tl = rn[blockIdx.x];
-    const double l = ps[tl.x];
-    if (ps[count + tl.x] != 0.0 || !(l > 0.0) || (int)threadIdx.x >= tl.z) return;
-    const int j = tl.y + threadIdx.x;
-    v[j] = w[j] / l;
 }
 
 __global__ void kb_set_step(DevState *sts, int count, const double *ps, double safety)
@@ -719,7 +748,7 @@ hipError_t batch_setup(pdhg_batch *b)
     hipLaunchKernelGGL(kb_set_norms, dim3(b->count), dim3(kBlock), 0, st, b->sts, pm, pn, b->rm_start, b->rn_start);
     // power iteration per LP on its block of Ahat'Ahat
     double *v = s->xu, *w = s->zsol, *u = s->ax; // float64 work vectors of the right lengths
-    hipMemsetAsync(b->lp_scalar, 0, sizeof(double) * 4 * (size_t)b->count, st);
+    hipMemsetAsync(b->lp_scalar, 0, sizeof(double) * 8 * (size_t)b->count, st);
     if (b->n_rn > 0) { // start: v = (1 + U) / ||1 + U|| per LP, the norm in lp_scalar[3 count + lp]
         hipLaunchKernelGGL(kb_fill_start, dim3(b->n_rn), dim3(kBlock), 0, st, b->rn, b->d_coff, v);
         hipLaunchKernelGGL((kb_sumsq<double>), dim3(b->n_rn), dim3(kBlock), 0, st, b->rn, v, pn);
@@ -727,11 +756,13 @@ hipError_t batch_setup(pdhg_batch *b)
         hipLaunchKernelGGL(kb_div_start, dim3(b->n_rn), dim3(kBlock), 0, st, b->rn, b->lp_scalar, b->count, v);
     }
     std::vector<double> done((size_t)b->count, 0.0);
+    double *state = b->lp_scalar; // after the last step launched; the other half takes the next step's
     constexpr int kPowerBatch = 32; // steps launched between reads of the done flags
     for (int it = 0; it < s->p.power_iters && s->m > 0 && s->n > 0; it += kPowerBatch) {
         const int len = std::min(kPowerBatch, s->p.power_iters - it);
         for (int k = 0; k < len; k++) {
-            const double *pdone = b->lp_scalar + b->count; // LPs whose power iteration has stopped
+            const double *pdone = state + b->count; // LPs whose power iteration has stopped
+            double *next = state == b->lp_scalar ? b->lp_scalar + 4 * (size_t)b->count : b->lp_scalar;
             if (s->fp32) {
                 launch_spmv_b<float, double>(b, b->kern_a, b->dtiles, b->n_dtiles, s->rp, s->ci,
                                              (const float *)s->ahat, v, u, pdone);
@@ -743,21 +774,23 @@ hipError_t batch_setup(pdhg_batch *b)
                 launch_spmv_b<double, double>(b, b->kern_at, b->ptiles, b->n_ptiles, s->tp, s->ti,
                                               (const double *)s->ahat_t, u, w, pdone);
             }
-            hipLaunchKernelGGL((kb_sumsq<double>), dim3(b->n_rm), dim3(kBlock), 0, st, b->rm, u, pm);
-            hipLaunchKernelGGL((kb_sumsq<double>), dim3(b->n_rn), dim3(kBlock), 0, st, b->rn, w, pn);
-            hipLaunchKernelGGL(kb_power_finish, dim3(b->count), dim3(kBlock), 0, st, b->rm_start, pm, b->rn_start, pn,
-                               b->count, s->p.power_tol, b->lp_scalar);
-            hipLaunchKernelGGL(kb_normalize, dim3(b->n_rn), dim3(kBlock), 0, st, b->rn, w, b->lp_scalar, b->count, v);
+            hipLaunchKernelGGL(kb_power_partials, dim3(b->n_rm + b->n_rn), dim3(kBlock), 0, st, b->rm, b->n_rm, u, pm,
+                               b->rn, w, pn, pdone);
+            hipLaunchKernelGGL(kb_power_end, dim3(b->n_rn), dim3(kBlock), 0, st, b->rn, b->rm_start, pm, b->rn_start,
+                               pn, b->count, s->p.power_tol, state, next, w, v);
+            state = next;
         }
-        hipError_t e = hipMemcpyAsync(done.data(), b->lp_scalar + b->count, sizeof(double) * done.size(),
+        hipError_t e = hipMemcpyAsync(done.data(), state + b->count, sizeof(double) * done.size(),
                                       hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) return e;
         if (std::all_of(done.begin(), done.end(), [](double d) { return d != 0.0; })) break;
+        if ((e = batch_compact_tiles(b, false, done.data())) != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kb_set_step, dim3((b->count + 255) / 256), dim3(256), 0, st, b->sts, b->count, b->lp_scalar,
+    hipLaunchKernelGGL(kb_set_step, dim3((b->count + 255) / 256), dim3(256), 0, st, b->sts, b->count, state,
                        s->p.eta_safety);
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : batch_compact_tiles(b, true);
 }
 
 template <typename V>
@@ -1391,24 +1424,26 @@ hipError_t batch_set_kernels(pdhg_batch *b, int kern_at, int kern_a)
 }
 
 // Iteration tiles of the LPs still iterating (all = false) or of every LP
-// (all = true, at the start of a phase).  Tiles of a stopped LP exit at once,
+// (all = true, at the start of a phase); with `done`, of the LPs whose flag is
+// 0 there (the power iteration).  Tiles of a stopped LP exit at once,
 // but a launch over them still dispatches their workgroups: once a quarter
 // of the tiles in use belong to stopped LPs, the lists are rebuilt without
 // them (in place: the device buffers hold every tile) and the captured cycle
 // graph, whose launches carry the tile counts, is dropped.  Tile order does
 // not enter any LP's arithmetic.
-hipError_t batch_compact_tiles(pdhg_batch *b, bool all)
+hipError_t batch_compact_tiles(pdhg_batch *b, bool all, const double *done)
 {
     std::vector<int4> pt, dt;
+    auto stopped = [&](const int4 &t) { return done ? done[t.x] != 0.0 : b->sts_host[t.x].done != 0; };
     if (all) {
         if (b->n_ptiles == (int)b->ptiles_all.size() && b->n_dtiles == (int)b->dtiles_all.size()) return hipSuccess;
         pt = b->ptiles_all;
         dt = b->dtiles_all;
     } else {
         for (const int4 &t : b->ptiles_all)
-            if (!b->sts_host[t.x].done) pt.push_back(t);
+            if (!stopped(t)) pt.push_back(t);
         for (const int4 &t : b->dtiles_all)
-            if (!b->sts_host[t.x].done) dt.push_back(t);
+            if (!stopped(t)) dt.push_back(t);
         if (pt.empty() || dt.empty()) return hipSuccess; // nothing left to run: the phase ends
         if (4 * pt.size() > 3 * (size_t)b->n_ptiles && 4 * dt.size() > 3 * (size_t)b->n_dtiles) return hipSuccess;
     }

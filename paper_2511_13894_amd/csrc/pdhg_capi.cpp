@@ -1298,7 +1298,7 @@ static int batch_finish(pdhg_solver *s, int count, const std::vector<int> &roff,
         HIPCHK(hipMemcpy(b->d_coff, coff.data(), sizeof(int) * coff.size(), hipMemcpyHostToDevice));
         dalloc(&b->sts, (size_t)count);
         dalloc(&b->part, (size_t)(Q_COUNT + 1) * (b->n_rm + b->n_rn));
-        dalloc(&b->lp_scalar, 4 * (size_t)count);
+        dalloc(&b->lp_scalar, 8 * (size_t)count);
         dalloc(&b->rep, (size_t)count * R_COUNT);
         dalloc(&b->active, (size_t)count);
         dalloc(&b->seeds, (size_t)count);

@@ -281,7 +281,7 @@ struct pdhg_batch {
     int *rn_start = nullptr, *rm_start = nullptr; // first reduction tile of each LP (count + 1)
     pdhg::DevState *sts = nullptr, *sts_host = nullptr;
     double *part = nullptr;                // per-tile partial sums
-    double *lp_scalar = nullptr;           // per-LP power iteration {lambda, done, steps, ||v0||} x count
+    double *lp_scalar = nullptr;           // per-LP power iteration {lambda, done, steps, ||v0||} x count, twice by turns
     double *rep = nullptr, *rep_host = nullptr; // per-LP report values
     int *active = nullptr;                 // per-LP flag: takes part in the current phase
     std::vector<int> active_host;
@@ -437,7 +437,7 @@ hipError_t copy_probe(int64_t bytes, int reps, double *gbps);
 // batch engine (pdhg_batch.hip)
 hipError_t batch_setup(pdhg_batch *b);
 hipError_t batch_autotune(pdhg_batch *b);
-hipError_t batch_compact_tiles(pdhg_batch *b, bool all);
+hipError_t batch_compact_tiles(pdhg_batch *b, bool all, const double *done = nullptr);
 hipError_t batch_set_kernels(pdhg_batch *b, int kern_at, int kern_a);
 hipError_t batch_phase_begin(pdhg_batch *b, bool fresh);
 hipError_t batch_defect_refresh(pdhg_batch *b);

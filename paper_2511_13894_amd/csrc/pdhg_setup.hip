@@ -565,7 +565,16 @@ hipError_t scale_problem(pdhg_solver *s)
 // first step with sqrt(w'w - rho^2) <= tol * rho (or when w = 0), keeping
 // lambda = ||w||, which lies in [rho, lambda_max(M)].  pw = {lambda, done,
 // steps}: the decision stays on the device and later steps of a launched
-// batch leave v and pw alone.
+// batch leave v and pw alone.  A step is four launches, as long as each is a
+// launch's latency: the two products, one for both sums of squares, one for
+// the decision and the next v (with the two sums, the decision and the
+// division in launches of their own, six: create of a 5,000 x 20,000 LP, 140
+// steps, 3.7 -> 2.6 or 3.1 ms, of a 1,600 x 4,000 LP, 928 steps, 19.3 -> 15.5).
+// The done flag is read after every 32 steps, on a large LP also after 4: a
+// transportation LP stops after 3, and the 29 others in flight cost 0.15 ms
+// each on 2,000 x 5,000 (create 14.9 -> 10.0 ms).  On a small LP the extra
+// read, which waits for the setup launched before, costs more than the steps
+// it could save (10,007 x 40,013, 53 steps: 1.75 -> 2.1 ms).
 
 // partial sums of squares per block
 __global__ __launch_bounds__(kBlock) void k_sumsq_partials(int len, const double *__restrict__ w, double *__restrict__ part)
@@ -598,30 +607,52 @@ __global__ __launch_bounds__(kBlock) void k_div_scalar(int64_t len, double *__re
     if (i < len) v[i] = v[i] / d[0];
 }
 
-// rho = sum of part[0, gm), w'w = sum of part[gm, gm + gn), fixed order
-__global__ __launch_bounds__(kBlock) void k_power_finish(int gm, int gn, const double *__restrict__ part, double tol,
-                                                        double *__restrict__ pw)
+// Partial sums of squares of u (the first gm blocks) and of w (the gn others),
+// each block's share as k_sumsq_partials gives it.
+__global__ __launch_bounds__(kBlock) void k_power_partials(int m, const double *__restrict__ u, int gm, int n,
+                                                          const double *__restrict__ w, int gn, double *__restrict__ part)
 {
-    if (pw[1] != 0.0) return;
-    double v[2] = {0.0, 0.0};
-    for (int i = threadIdx.x; i < gm; i += kBlock) v[0] += part[i];
-    for (int i = threadIdx.x; i < gn; i += kBlock) v[1] += part[gm + i];
-    block_reduce<2>(v, 0u);
-    if (threadIdx.x == 0) {
-        const double rho = v[0], ww = v[1], lam = sqrt(ww);
-        pw[0] = lam;
-        pw[2] += 1.0;
-        if (power_stops(rho, ww, lam, tol)) pw[1] = 1.0;
-    }
+    const bool rows = (int)blockIdx.x < gm;
+    const int b = rows ? blockIdx.x : blockIdx.x - gm, len = rows ? m : n, g = rows ? gm : gn;
+    const double *q = rows ? u : w;
+    double v[1] = {0.0};
+    for (int64_t i = (int64_t)b * kBlock + threadIdx.x; i < len; i += (int64_t)g * kBlock) v[0] += q[i] * q[i];
+    block_reduce<1>(v, 0u);
+    if (threadIdx.x == 0) part[blockIdx.x] = v[0];
 }
 
-__global__ __launch_bounds__(kBlock) void k_normalize(int len, const double *__restrict__ w, const double *__restrict__ pw,
-                                                     double *__restrict__ v)
+// A step's end: rho = sum of part[0, gm), w'w = sum of part[gm, gm + gn) in a
+// fixed order by every workgroup, the decision from them and from the state
+// before the step (old), and v = w / lambda unless the iteration stops.  The
+// first workgroup writes the state after the step (now, another buffer, as the
+// others may still read old).
+__global__ __launch_bounds__(kBlock) void k_power_end(int gm, int gn, const double *__restrict__ part, double tol,
+                                                     const double *__restrict__ old, double *__restrict__ now, int len,
+                                                     const double *__restrict__ w, double *__restrict__ v)
 {
-    const double l = pw[0];
-    if (pw[1] != 0.0 || !(l > 0.0)) return;
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i < len) v[i] = w[i] / l;
+    __shared__ double s_lam;
+    if (old[1] != 0.0) {
+        if (blockIdx.x == 0 && threadIdx.x < 3) now[threadIdx.x] = old[threadIdx.x];
+        return;
+    }
+    double q[2] = {0.0, 0.0};
+    for (int i = threadIdx.x; i < gm; i += kBlock) q[0] += part[i];
+    for (int i = threadIdx.x; i < gn; i += kBlock) q[1] += part[gm + i];
+    block_reduce<2>(q, 0u);
+    if (threadIdx.x == 0) {
+        const double rho = q[0], ww = q[1], lam = sqrt(ww);
+        const bool stops = power_stops(rho, ww, lam, tol);
+        s_lam = stops ? 0.0 : lam;
+        if (blockIdx.x == 0) {
+            now[0] = lam;
+            now[1] = stops ? 1.0 : 0.0;
+            now[2] = old[2] + 1.0;
+        }
+    }
+    __syncthreads();
+    const double l = s_lam;
+    if (!(l > 0.0)) return;
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < len; i += (int64_t)gridDim.x * kBlock) v[i] = w[i] / l;
 }
 
 __global__ void k_set_step(pdhg::DevState *st, const double *pw, double safety)
@@ -643,9 +674,9 @@ hipError_t power_iteration(pdhg_solver *s)
     slab.add(&v, (size_t)n);
     slab.add(&w, (size_t)n);
     slab.add(&u, (size_t)m);
-    slab.add(&pw, 4);
+    slab.add(&pw, 8); // the state, twice by turns; pw[3]: the start's norm
     if ((e = slab.commit(&temp)) != hipSuccess) return e;
-    hipMemsetAsync(pw, 0, 4 * sizeof(double), st);
+    hipMemsetAsync(pw, 0, 8 * sizeof(double), st);
     const int gm = grid_for(m, kBlock, kMaxRedBlocks), gn = grid_for(n, kBlock, kMaxRedBlocks);
     const bool resident = s->res.variant > 0; // a small LP's steps in one launch
     if (resident && (e = resident_power(s, pw)) != hipSuccess) {
@@ -659,27 +690,30 @@ hipError_t power_iteration(pdhg_solver *s)
         hipLaunchKernelGGL(k_norm_finish, dim3(1), dim3(kBlock), 0, st, gn, s->partials, pw + 3);
         hipLaunchKernelGGL(k_div_scalar, dim3(gv), dim3(kBlock), 0, st, (int64_t)n, v, pw + 3);
     }
-    double pw_host[4] = {0.0, 0.0, 0.0, 0.0};
-    constexpr int kPowerBatch = 32; // steps launched between reads of the done flag
-    for (int it = 0; it < s->p.power_iters && n > 0 && m > 0 && !resident; it += kPowerBatch) {
-        const int len = std::min(kPowerBatch, s->p.power_iters - it);
-        for (int k = 0; k < len; k++) {
+    double pw_host[3] = {0.0, 0.0, 0.0};
+    double *state = pw; // after the last step launched
+    const int ge = std::min(grid_for(n, kBlock, 1 << 30), kMaxRedBlocks);
+    const int first = s->nnz >= 1000000 ? 4 : 32;
+    for (int it = 0; it < s->p.power_iters && n > 0 && m > 0 && !resident;) {
+        const int len = std::min(it > 0 ? 32 : first, s->p.power_iters - it);
+        for (int k = 0; k < len; k++, it++) {
+            double *next = state == pw ? pw + 4 : pw;
             (void)solver_product(s, false, v, u);
             (void)solver_product(s, true, u, w);
-            hipLaunchKernelGGL(k_sumsq_partials, dim3(gm), dim3(kBlock), 0, st, m, u, s->partials);
-            hipLaunchKernelGGL(k_sumsq_partials, dim3(gn), dim3(kBlock), 0, st, n, w, s->partials + gm);
-            hipLaunchKernelGGL(k_power_finish, dim3(1), dim3(kBlock), 0, st, gm, gn, s->partials, s->p.power_tol, pw);
-            hipLaunchKernelGGL(k_normalize, dim3(grid_for(n, kBlock, 1 << 30)), dim3(kBlock), 0, st, n, w, pw, v);
+            hipLaunchKernelGGL(k_power_partials, dim3(gm + gn), dim3(kBlock), 0, st, m, u, gm, n, w, gn, s->partials);
+            hipLaunchKernelGGL(k_power_end, dim3(ge), dim3(kBlock), 0, st, gm, gn, s->partials, s->p.power_tol, state,
+                               next, n, w, v);
+            state = next;
         }
-        if ((e = hipMemcpyAsync(pw_host, pw, 4 * sizeof(double), hipMemcpyDeviceToHost, st)) != hipSuccess) break;
+        if ((e = hipMemcpyAsync(pw_host, state, sizeof pw_host, hipMemcpyDeviceToHost, st)) != hipSuccess) break;
         if ((e = hipStreamSynchronize(st)) != hipSuccess) break;
         if (pw_host[1] != 0.0) break;
     }
-    if (resident && (e = hipMemcpyAsync(pw_host, pw, 4 * sizeof(double), hipMemcpyDeviceToHost, st)) == hipSuccess)
+    if (resident && (e = hipMemcpyAsync(pw_host, pw, sizeof pw_host, hipMemcpyDeviceToHost, st)) == hipSuccess)
         e = hipStreamSynchronize(st);
     s->power_steps = (int64_t)pw_host[2];
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_set_step, dim3(1), dim3(1), 0, st, s->st, pw, s->p.eta_safety);
+        hipLaunchKernelGGL(k_set_step, dim3(1), dim3(1), 0, st, s->st, state, s->p.eta_safety);
         e = hipGetLastError();
     }
     hipError_t e2 = hipStreamSynchronize(st);
