@@ -18,6 +18,8 @@ struct pdhg_mlp {
     int max_waves = 0;
     double *loss_acc = nullptr;
     int64_t adam_t = 0;
+    int device = -1;               // the networks of one device order their own streams' forward passes (mlp_order)
+    hipEvent_t order = nullptr;    // the passes enqueued on `stream` so far
 };
 
 namespace pdhg {
@@ -32,4 +34,7 @@ hipError_t mlp_train_step(pdhg_mlp *net, const short *F, const float *Y, const i
 // device address of the no-allocation forward's staging array on the current
 // device (looked up once per device)
 hipError_t mlp_scratch_setup();
+// the network's device and event for the order of own-stream forward passes
+hipError_t mlp_order_setup(pdhg_mlp *net);
+void mlp_order_forget(const pdhg_mlp *net); // before its stream goes
 } // namespace pdhg

@@ -88,6 +88,7 @@ int pdhg_mlp_create(uint64_t seed, pdhg_mlp **out)
     if (!net) return fail(PDHG_ERR_OOM, "host allocation failed");
     try {
         CHK(hipStreamCreate(&net->stream));
+        CHK(mlp_order_setup(net));
         for (float **q : {&net->p, &net->m, &net->v, &net->grad}) CHK(hipMalloc(q, sizeof(float) * MLP_NPARAMS));
         CHK(hipMalloc(&net->w1b, sizeof(short) * 1024));
         CHK(hipMalloc(&net->w2b, sizeof(short) * 4096));
@@ -111,7 +112,9 @@ int pdhg_mlp_create(uint64_t seed, pdhg_mlp **out)
 void pdhg_mlp_destroy(pdhg_mlp *net)
 {
     if (!net) return;
+    mlp_order_forget(net);
     if (net->stream) (void)hipStreamSynchronize(net->stream);
+    if (net->order) (void)hipEventDestroy(net->order);
     for (void *q : {(void *)net->p, (void *)net->m, (void *)net->v, (void *)net->grad, (void *)net->w1b,
                     (void *)net->w2b, (void *)net->w3b, (void *)net->w2tb, (void *)net->part, (void *)net->lossp, (void *)net->loss_acc})
         if (q) (void)hipFree(q);

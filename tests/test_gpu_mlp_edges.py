@@ -59,3 +59,26 @@ def test_forward_noalloc_on_element_aligned_and_overlapping_buffers(n, shift):
             np.testing.assert_array_equal(got[at + n:], host[at + n:])
     finally:
         hip.hipFree(buf)
+
+
+@pytest.mark.parametrize("n", [3000, 20000, 65536])
+def test_forward_noalloc_of_networks_by_turns_into_one_buffer(n):
+    """Passes on the networks' own streams run in the order of the calls: the
+    last one's logits are what the buffer holds."""
+    hip = pdhg._hip_runtime()
+    f, _ = _data(n, 5)
+    for seed in range(6):
+        nets = [pdhg.Mlp(seed + k) for k in (10, 20, 30)]
+        want = nets[0].forward(f)
+        got = np.empty(n, np.float32)
+        df, dl = C.c_void_p(), C.c_void_p()
+        assert hip.hipMalloc(C.byref(df), f.nbytes) == 0
+        assert hip.hipMalloc(C.byref(dl), got.nbytes) == 0
+        assert hip.hipMemcpy(df, f.ctypes.data_as(C.c_void_p), f.nbytes, 1) == 0
+        for k in (0, 1, 2, 0, 1, 0):
+            nets[k].forward_noalloc(df.value, n, dl.value)
+        del nets[1]  # its stream may be the last one waited for
+        assert hip.hipDeviceSynchronize() == 0
+        assert hip.hipMemcpy(got.ctypes.data_as(C.c_void_p), dl, got.nbytes, 2) == 0
+        np.testing.assert_array_equal(got, want)
+        assert hip.hipFree(df) == 0 and hip.hipFree(dl) == 0
