@@ -472,9 +472,9 @@ int pdhg_mlp_forward(pdhg_mlp *net, const float *features, int64_t n, float *log
 /* pdhg_mlp_forward for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops): features[n x 16] and
  * logits[n] are the caller's device buffers, on the device the network was
- * created on; the work is enqueued on `stream` (a hipStream_t, NULL: the
- * network's own stream, where the passes of all networks of a device run in
- * the order of their calls) and the call returns without waiting.  n is at most
+ * created on; the work is enqueued on `stream` (a hipStream_t, NULL: one of
+ * the library's, on which the passes of a device's networks run in the order
+ * of their calls) and the call returns without waiting.  n is at most
  * 65536 per call (INVALID_ARG beyond); no allocation, no synchronisation.
  * Where logits overlaps features, a bfloat16 copy of the features is staged
  * in a fixed 2 MiB device array per GPU, which such calls share: those that

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
 
 #include "pdhg.h"
@@ -18,8 +19,9 @@ struct pdhg_mlp {
     int max_waves = 0;
     double *loss_acc = nullptr;
     int64_t adam_t = 0;
-    int device = -1;               // the networks of one device order their own streams' forward passes (mlp_order)
-    hipEvent_t order = nullptr;    // the passes enqueued on `stream` so far
+    int device = -1;
+    hipStream_t pass = nullptr; // forward passes of callers who name no stream: one stream for a device's networks
+    std::atomic<bool> passed{false}; // such passes may be in flight
 };
 
 namespace pdhg {
@@ -34,7 +36,8 @@ hipError_t mlp_train_step(pdhg_mlp *net, const short *F, const float *Y, const i
 // device address of the no-allocation forward's staging array on the current
 // device (looked up once per device)
 hipError_t mlp_scratch_setup();
-// the network's device and event for the order of own-stream forward passes
-hipError_t mlp_order_setup(pdhg_mlp *net);
-void mlp_order_forget(const pdhg_mlp *net); // before its stream goes
+// take and give back the device's shared pass stream; wait for the passes on it
+hipError_t mlp_pass_open(pdhg_mlp *net);
+void mlp_pass_close(pdhg_mlp *net);
+hipError_t mlp_pass_wait(pdhg_mlp *net);
 } // namespace pdhg

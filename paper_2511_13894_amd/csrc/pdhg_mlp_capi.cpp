@@ -88,7 +88,7 @@ int pdhg_mlp_create(uint64_t seed, pdhg_mlp **out)
     if (!net) return fail(PDHG_ERR_OOM, "host allocation failed");
     try {
         CHK(hipStreamCreate(&net->stream));
-        CHK(mlp_order_setup(net));
+        CHK(mlp_pass_open(net));
         for (float **q : {&net->p, &net->m, &net->v, &net->grad}) CHK(hipMalloc(q, sizeof(float) * MLP_NPARAMS));
         CHK(hipMalloc(&net->w1b, sizeof(short) * 1024));
         CHK(hipMalloc(&net->w2b, sizeof(short) * 4096));
@@ -112,9 +112,9 @@ int pdhg_mlp_create(uint64_t seed, pdhg_mlp **out)
 void pdhg_mlp_destroy(pdhg_mlp *net)
 {
     if (!net) return;
-    mlp_order_forget(net);
+    (void)mlp_pass_wait(net);
     if (net->stream) (void)hipStreamSynchronize(net->stream);
-    if (net->order) (void)hipEventDestroy(net->order);
+    mlp_pass_close(net);
     for (void *q : {(void *)net->p, (void *)net->m, (void *)net->v, (void *)net->grad, (void *)net->w1b,
                     (void *)net->w2b, (void *)net->w3b, (void *)net->w2tb, (void *)net->part, (void *)net->lossp, (void *)net->loss_acc})
         if (q) (void)hipFree(q);
@@ -126,6 +126,7 @@ int pdhg_mlp_set_params(pdhg_mlp *net, const float *params)
 {
     if (!net || !params) return fail(PDHG_ERR_INVALID_ARG, "NULL argument");
     try {
+        CHK(mlp_pass_wait(net)); // they still read the weights
         CHK(hipMemcpyAsync(net->p, params, sizeof(float) * MLP_NPARAMS, hipMemcpyHostToDevice, net->stream));
         CHK(hipMemsetAsync(net->m, 0, sizeof(float) * MLP_NPARAMS, net->stream));
         CHK(hipMemsetAsync(net->v, 0, sizeof(float) * MLP_NPARAMS, net->stream));
@@ -142,6 +143,7 @@ int pdhg_mlp_get_params(pdhg_mlp *net, float *params)
 {
     if (!net || !params) return fail(PDHG_ERR_INVALID_ARG, "NULL argument");
     try {
+        CHK(mlp_pass_wait(net));
         CHK(hipMemcpyAsync(params, net->p, sizeof(float) * MLP_NPARAMS, hipMemcpyDeviceToHost, net->stream));
         CHK(hipStreamSynchronize(net->stream));
     } catch (const HipFail &f) {
@@ -155,6 +157,7 @@ int pdhg_mlp_forward(pdhg_mlp *net, const float *features, int64_t n, float *log
     if (!net || (n > 0 && (!features || !logits)) || n < 0) return fail(PDHG_ERR_INVALID_ARG, "bad arguments");
     if (n == 0) return PDHG_OK;
     try {
+        CHK(mlp_pass_wait(net));
         DevSet d;
         upload(net, d, features, nullptr, n);
         float *dl = nullptr;
@@ -176,6 +179,7 @@ int pdhg_mlp_gradient(pdhg_mlp *net, const float *features, const float *labels,
     if (!net || !features || !labels || !grad || n < 1 || n > kMaxBatch)
         return fail(PDHG_ERR_INVALID_ARG, "bad arguments (1 <= n <= 65536)");
     try {
+        CHK(mlp_pass_wait(net));
         DevSet d;
         upload(net, d, features, labels, n);
         std::vector<int> idx((size_t)n);
@@ -219,6 +223,7 @@ int pdhg_mlp_train(pdhg_mlp *net, const float *features, const float *labels, in
     if (t.batch < 1 || t.batch > kMaxBatch || t.epochs < 0) return fail(PDHG_ERR_INVALID_ARG, "bad training parameters");
     const double t0 = now_s();
     try {
+        CHK(mlp_pass_wait(net));
         // positive-class weight N_neg / N_pos unless given
         double pw = t.pos_weight;
         if (!(pw > 0.0)) {

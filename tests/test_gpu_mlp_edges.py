@@ -77,7 +77,7 @@ def test_forward_noalloc_of_networks_by_turns_into_one_buffer(n):
         assert hip.hipMemcpy(df, f.ctypes.data_as(C.c_void_p), f.nbytes, 1) == 0
         for k in (0, 1, 2, 0, 1, 0):
             nets[k].forward_noalloc(df.value, n, dl.value)
-        del nets[1]  # its stream may be the last one waited for
+        del nets[1]  # the networks share the stream
         assert hip.hipDeviceSynchronize() == 0
         assert hip.hipMemcpy(got.ctypes.data_as(C.c_void_p), dl, got.nbytes, 2) == 0
         np.testing.assert_array_equal(got, want)
