@@ -18,6 +18,8 @@
 // need the activations with the variable index as K; those tiles go through
 // LDS.
 #include <cmath>
+
+#include <algorithm>
 #include <mutex>
 #include <string>
 
@@ -99,11 +101,13 @@ __device__ __forceinline__ bf16x4 load_features(const float *__restrict__ F, int
     return bf16x4{f2bf(f[0]), f2bf(f[1]), f2bf(f[2]), f2bf(f[3])};
 }
 
-// One wave per tile of 16 variables: a call of 65,536 variables is one round
-// of 4,096 waves and is bound by its chain of loads and matrix steps, so the
-// features, weights and biases go out together, as 8- and 16-byte loads (11.9
-// us per call with a separate bfloat16 pass and 2-byte weight loads, 9.1 us
-// now, host calls included).
+// A wave takes tiles of 16 variables by turns.  A call is bound by its chain of
+// loads and matrix steps, so the features, weights and biases go out together,
+// as 8- and 16-byte loads; and where there are more workgroups than CUs, by the
+// weights, which every wave reads: 32 loads of 16 lines each, more of the CU's
+// cache than the features and the arithmetic of a tile (forward_grid).  65,536
+// variables, host calls included: 11.9 us per call with a separate bfloat16
+// pass and 2-byte weight loads, 9.1-11.2 with one tile a wave, 6.4 with four.
 template <typename FT>
 __global__ __launch_bounds__(kBlock) void k_mlp_forward(const FT *__restrict__ F, int64_t N, MlpW w,
                                                        float *__restrict__ logits)
@@ -519,13 +523,24 @@ hipError_t mlp_features_to_bf16(hipStream_t st, const float *src, short *dst, in
     return hipGetLastError();
 }
 
+// Workgroups of a forward pass: one tile a wave until every CU has a workgroup,
+// then as many tiles a wave as keep it at one, at most 8 (16 past a million
+// variables, where the chain of a wave's tiles hides behind the other waves).
+// us by rocprofv3, one tile a wave -> this rule: 65,536 variables 11.4 -> 6.0,
+// 131,072 20.8 -> 8.9 (9.2 with 4 tiles, 13.5 with 16), 262,144 39.8 -> 13.0
+// (15.1, 14.3), 1,048,576 152 -> 34 (38 with 8), 4,194,304 598 -> 108 (126).
+static int forward_grid(int64_t tiles)
+{
+    const int64_t full = (tiles + 3) / 4; // one tile a wave
+    const int64_t most = full < 16384 ? 8 : 16, per = std::min(most, (full + 255) / 256);
+    return grid_for((full + per - 1) / per, 1, 1 << 20);
+}
+
 template <typename FT>
 static hipError_t forward_impl(const pdhg_mlp *net, hipStream_t st, const FT *F, int64_t N, float *logits)
 {
     if (N <= 0) return hipSuccess;
-    const int64_t tiles = (N + 15) / 16;
-    const int grid = grid_for((tiles + 3) / 4, 1, 1 << 20);
-    hipLaunchKernelGGL((k_mlp_forward<FT>), dim3(grid), dim3(kBlock), 0, st, F, N, weights(net), logits);
+    hipLaunchKernelGGL((k_mlp_forward<FT>), dim3(forward_grid((N + 15) / 16)), dim3(kBlock), 0, st, F, N, weights(net), logits);
     return hipGetLastError();
 }
 

@@ -82,3 +82,14 @@ def test_forward_noalloc_of_networks_by_turns_into_one_buffer(n):
         assert hip.hipMemcpy(got.ctypes.data_as(C.c_void_p), dl, got.nbytes, 2) == 0
         np.testing.assert_array_equal(got, want)
         assert hip.hipFree(df) == 0 and hip.hipFree(dl) == 0
+
+
+@pytest.mark.parametrize("n", [16384, 16385, 32769, 65520, 131089, 262145, 1048593])
+def test_forward_of_many_tiles_a_wave_equals_that_of_its_parts(n):
+    """One to sixteen tiles a wave, the last one of each wave missing or partial:
+    a variable's logit does not depend on the others."""
+    f, _ = _data(n, n)
+    net = pdhg.Mlp(5)
+    whole = net.forward(f)
+    parts = np.concatenate([net.forward(f[k:k + 9999]) for k in range(0, n, 9999)])
+    np.testing.assert_array_equal(whole, parts)
