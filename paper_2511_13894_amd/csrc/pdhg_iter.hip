@@ -232,16 +232,19 @@ __device__ __forceinline__ double row_block_sum(int beg, int end, const int *__r
 // against 8.16 as waves).  Rows that gather next to the row before them (the
 // coupling rows of a multicommodity network, one column per commodity) share
 // gathered lines when more rows than entries sit in one load: with a quarter
-// of the entries in such rows waves win again once the launch is far past one
-// generation (256,000 rows 42.6 -> 40.2 (39.0 -> 34.1), 400,000 rows 63.6 ->
-// 60.0 (58.5 -> 50.3); 128,000 rows, 8,000 waves: 24.8 -> 25.4 (22.6 -> 22.9)).
+// of the entries in such rows waves win again from two to four generations of
+// them (256,000 rows, 16,000 waves, 42.6 -> 40.2 (39.0 -> 34.1), 400,000 rows
+// 63.4 -> 59.4 (58.7 -> 50.1); either side of that 128,000 rows 24.8 -> 25.4
+// (22.6 -> 22.9), 560,000 rows 92.8 -> 96.4 (68.1 -> 68.6), 800,000 rows 144
+// -> 150 (109.3 -> 111.0): the upper line is measured, its cause not found).
 bool uses_waves(const pdhg_solver *s, int kern, bool dual)
 {
     if (kern != -32 && kern != -64 && kern != -128 && kern != -256) return false;
     const int G = kWaveTile / -kern;
     if ((dual ? s->longest_row : s->longest_col) > kWaveTerms * G) return false;
     const int64_t waves = ((int64_t)(dual ? s->m : s->n) * G + 63) / 64;
-    return waves <= kWavesResident || (dual && waves >= 2 * kWavesResident && 4 * (int64_t)s->beside >= s->nnz);
+    return waves <= kWavesResident || (dual && waves >= 2 * kWavesResident && waves <= 4 * kWavesResident &&
+                                       4 * (int64_t)s->beside >= s->nnz);
 }
 
 // --------------------------------------------- short rows, one wave each ---
