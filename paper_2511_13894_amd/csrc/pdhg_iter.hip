@@ -229,22 +229,26 @@ __device__ __forceinline__ double row_block_sum(int beg, int end, const int *__r
 // waves) 30.0 -> 30.5 (28.9 -> 28.8), 400,000 (25,000) 118.6 -> 119.2 (84.7
 // -> 89.9).  A row of many more entries than lanes is a chain the wave's other
 // lanes wait for: power-law columns of up to 200 entries stay in tiles (7.97
-// against 8.16 as waves).  Rows that gather next to the row before them (the
-// coupling rows of a multicommodity network, one column per commodity) share
-// gathered lines when more rows than entries sit in one load: with a quarter
-// of the entries in such rows waves win again from two to four generations of
-// them (256,000 rows, 16,000 waves, 42.6 -> 40.2 (39.0 -> 34.1), 400,000 rows
-// 63.4 -> 59.4 (58.7 -> 50.1); either side of that 128,000 rows 24.8 -> 25.4
-// (22.6 -> 22.9), 560,000 rows 92.8 -> 96.4 (68.1 -> 68.6), 800,000 rows 144
-// -> 150 (109.3 -> 111.0): the upper line is measured, its cause not found).
+// against 8.16 as waves).  Where the rows change kind along the matrix (a
+// multicommodity network's node rows, then its coupling rows, each of which
+// gathers next to the row before it), a launch of tiles that is too small to
+// be dealt to the XCDs in chunks (xcd_block) gives them unequal work, and its
+// waves, four times as many, are dealt: 131,200 rows (2,050 tiles) 25.9 -> 23.8
+// (24.1 -> 20.5), 256,000 rows 42.6 -> 40.2 (39.0 -> 34.1), 400,000 rows 63.4
+// -> 59.4 (58.7 -> 50.1), 512,000 rows (8,000 tiles) 83.2 -> 77.1 (72.4 ->
+// 62.3); with tiles dealt in chunks instead, 256,000 and 400,000 rows 41.0
+// (35.0) and 58.4 (50.5), but one kind of rows loses (100,000 power-law rows
+// 38.7 -> 39.0 (35.8 -> 36.1)).  Where the tiles are dealt already waves lose:
+// 560,000 rows 92.8 -> 96.4 (68.1 -> 68.6), 800,000 rows 144 -> 150 (109.3 ->
+// 111.0); where neither is, too: 128,000 rows 24.8 -> 25.4 (22.6 -> 22.9).
 bool uses_waves(const pdhg_solver *s, int kern, bool dual)
 {
     if (kern != -32 && kern != -64 && kern != -128 && kern != -256) return false;
     const int G = kWaveTile / -kern;
     if ((dual ? s->longest_row : s->longest_col) > kWaveTerms * G) return false;
     const int64_t waves = ((int64_t)(dual ? s->m : s->n) * G + 63) / 64;
-    return waves <= kWavesResident || (dual && waves >= 2 * kWavesResident && waves <= 4 * kWavesResident &&
-                                       4 * (int64_t)s->beside >= s->nnz);
+    const bool dealt = waves >= kXcdChunkMin && (s->m - kern - 1) / -kern < kXcdChunkMin; // waves, but not tiles
+    return waves <= kWavesResident || (dual && dealt && 4 * (int64_t)s->beside >= s->nnz);
 }
 
 // --------------------------------------------- short rows, one wave each ---
