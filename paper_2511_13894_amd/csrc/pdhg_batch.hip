@@ -6,6 +6,7 @@
 // DevState (step sizes, Halpern counter, restart state, done flag), its own
 // scaling, step size and checks; checks reduce per-tile partial sums of each
 // LP in a fixed order, so an LP's trajectory does not depend on the others.
+#include <climits>
 #include <cmath>
 
 #include <algorithm>
@@ -162,7 +163,7 @@ __global__ __launch_bounds__(64) void kb_dual_wave(const int4 *__restrict__ tile
 // 19.5 (the LPs gather from short vectors, so tiles wait less).
 static bool batch_waves(const pdhg_batch *b, int kern, int tiles, bool dual)
 {
-    if (kern != -32 && kern != -64 && kern != -128 && kern != -256) return false;
+    if ((kern != -32 && kern != -64 && kern != -128 && kern != -256) || b->s->nnz > INT_MAX - kWaveAhead) return false;
     if ((dual ? b->s->longest_row : b->s->longest_col) > kWaveTerms * (kWaveTile / -kern)) return false;
     return kTileWaves * (int64_t)tiles <= kWavesResident / 2;
 }

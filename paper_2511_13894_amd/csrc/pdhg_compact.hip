@@ -92,7 +92,8 @@ __global__ __launch_bounds__(kBlock) void k_row_free_count(int m, const int *__r
         return;
     }
     int c = 0;
-    for (int e = rp[i] + lane; e < rp[i + 1]; e += 64) c += flag[ci[e]];
+    const unsigned end = rp[i + 1];
+    for (unsigned e = rp[i] + lane; e < end; e += 64) c += flag[ci[e]];
     c = group_sum<64>(c);
     if (lane == 0) cnt[i] = c;
 }
@@ -110,9 +111,10 @@ __global__ __launch_bounds__(kBlock) void k_copy_rows(int m, const int *__restri
     if (i >= m) return;
     const uint64_t below = (1ull << lane) - 1ull;
     int o = rpc[i];
-    for (int e0 = rp[i]; e0 < rp[i + 1]; e0 += 64) {
-        const int e = e0 + lane;
-        const bool in = e < rp[i + 1];
+    const unsigned end = rp[i + 1];
+    for (unsigned e0 = rp[i]; e0 < end; e0 += 64) {
+        const unsigned e = e0 + lane;
+        const bool in = e < end;
         const int col = in ? ci[e] : 0;
         const bool keep = in && flag[col] != 0;
         const uint64_t mask = __ballot(keep);

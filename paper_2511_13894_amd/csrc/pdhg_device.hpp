@@ -132,19 +132,21 @@ __device__ __forceinline__ int xcd_block(int bid, int nblk)
 // and before they are waited for the next round's index and value loads, so a
 // round costs one gather's latency and the index loads hide behind it.
 // Positions past the end reload the last entry; their terms are not added.
+// What is compared is the entries left, never a position ahead of the end: a
+// model may hold 2^31 - 1 entries, and such a position would wrap.
 template <int L, int U, typename ACC, typename I, typename VM, typename VX>
 __device__ __forceinline__ ACC lane_rounds(int beg, int end, int lane, const I *__restrict__ idx,
                                            const VM *__restrict__ val, const VX *__restrict__ x)
 {
     ACC acc = 0;
+    int left = end - beg - lane;
+    if (left <= 0) return acc;
     int e = beg + lane;
-    if (e >= end) return acc;
-    const int last = end - 1;
     I i[U];
     VM v[U];
 #pragma unroll
     for (int u = 0; u < U; u++) {
-        const int k = e + u * L < last ? e + u * L : last;
+        const int k = e + (u * L < left ? u * L : left - 1);
         i[u] = idx[k];
         v[u] = val[k];
     }
@@ -155,21 +157,21 @@ __device__ __forceinline__ ACC lane_rounds(int beg, int end, int lane, const I *
         for (int u = 0; u < U; u++) g[u] = x[i[u]];
 #pragma unroll
         for (int u = 0; u < U; u++) w[u] = (ACC)v[u];
-        const int n0 = e + U * L;
-        if (!__builtin_amdgcn_ballot_w64(n0 + (U - 1) * L >= end)) { // a full round for every lane of the wave still here
+        if (!__builtin_amdgcn_ballot_w64(left <= (2 * U - 1) * L)) { // a full round for every lane of the wave still here
+            e += U * L;
+            left -= U * L;
 #pragma unroll
-            for (int u = 0; u < U; u++) i[u] = idx[n0 + u * L];
+            for (int u = 0; u < U; u++) i[u] = idx[e + u * L];
 #pragma unroll
-            for (int u = 0; u < U; u++) v[u] = val[n0 + u * L];
+            for (int u = 0; u < U; u++) v[u] = val[e + u * L];
 #pragma unroll
             for (int u = 0; u < U; u++) acc += w[u] * (ACC)g[u];
-            e = n0;
             continue;
         }
-        if (__builtin_amdgcn_ballot_w64(n0 < end)) {
+        if (__builtin_amdgcn_ballot_w64(left > U * L)) {
 #pragma unroll
             for (int u = 0; u < U; u++) {
-                const int k = n0 + u * L < last ? n0 + u * L : last;
+                const int k = e + ((U + u) * L < left ? (U + u) * L : left - 1);
                 i[u] = idx[k];
                 v[u] = val[k];
             }
@@ -177,9 +179,10 @@ __device__ __forceinline__ ACC lane_rounds(int beg, int end, int lane, const I *
         acc += w[0] * (ACC)g[0];
 #pragma unroll
         for (int u = 1; u < U; u++)
-            if (e + u * L < end) acc += w[u] * (ACC)g[u];
-        if (n0 >= end) return acc;
-        e = n0;
+            if (u * L < left) acc += w[u] * (ACC)g[u];
+        if (left <= U * L) return acc;
+        e += U * L;
+        left -= U * L;
     }
 }
 

@@ -2,6 +2,7 @@
 // extrapolation and Halpern averaging), the periodic check (residuals, gap,
 // weighted KKT, restart and primal-weight update, termination), the corner
 // push setup of Algorithm 1, and float64 KKT reports on the original model.
+#include <climits>
 #include <cmath>
 #include <cstdio>
 #include <vector>
@@ -175,9 +176,9 @@ __global__ __launch_bounds__(kBlock) void k_row_adjacent(int m, const int *__res
     const int64_t w = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
     const int lane = threadIdx.x & 63;
     if (w >= m) return;
-    const int beg = rp[w], end = rp[w + 1];
+    const unsigned beg = rp[w], end = rp[w + 1]; // unsigned: e passes the end by up to 64
     int c = 0;
-    for (int e = beg + lane; e + 1 < end; e += 64) c += ci[e + 1] == ci[e] + 1 ? 1 : 0;
+    for (unsigned e = beg + lane; e + 1 < end; e += 64) c += ci[e + 1] == ci[e] + 1 ? 1 : 0;
     c = group_sum<64>(c);
     if (lane == 0) adj[w] = c;
 }
@@ -192,15 +193,14 @@ __device__ __forceinline__ double row_block_sum(int beg, int end, const int *__r
                                                 const VM *__restrict__ val, const VV *__restrict__ vec)
 {
     double acc = 0.0;
-    for (int e0 = beg + (int)threadIdx.x; e0 < end; e0 += 4 * kBlock) {
+    for (int left = end - beg - (int)threadIdx.x; left > 0; left -= 4 * kBlock) { // entries left: lane_rounds
         int id[4];
         double v[4], g[4];
         // every lane loads: positions past the row's end reload its last
-        // entry (e0 < end here), so no load is merged with a fallback value
+        // entry (left > 0 here), so no load is merged with a fallback value
 #pragma unroll
         for (int u = 0; u < 4; u++) {
-            const int e = e0 + u * kBlock;
-            const int ec = e < end ? e : end - 1;
+            const int ec = end - left + (u * kBlock < left ? u * kBlock : left - 1);
             id[u] = idx[ec];
             v[u] = (double)val[ec];
         }
@@ -208,7 +208,7 @@ __device__ __forceinline__ double row_block_sum(int beg, int end, const int *__r
         for (int u = 0; u < 4; u++) g[u] = (double)vec[id[u]];
 #pragma unroll
         for (int u = 0; u < 4; u++)
-            if (e0 + u * kBlock < end) acc += v[u] * g[u];
+            if (u * kBlock < left) acc += v[u] * g[u];
     }
     double q[1] = {acc};
     block_reduce<1>(q, 0u);
@@ -243,7 +243,7 @@ __device__ __forceinline__ double row_block_sum(int beg, int end, const int *__r
 // 111.0); where neither is, too: 128,000 rows 24.8 -> 25.4 (22.6 -> 22.9).
 bool uses_waves(const pdhg_solver *s, int kern, bool dual)
 {
-    if (kern != -32 && kern != -64 && kern != -128 && kern != -256) return false;
+    if ((kern != -32 && kern != -64 && kern != -128 && kern != -256) || s->nnz > INT_MAX - kWaveAhead) return false;
     const int G = kWaveTile / -kern;
     if ((dual ? s->longest_row : s->longest_col) > kWaveTerms * G) return false;
     const int64_t waves = ((int64_t)(dual ? s->m : s->n) * G + 63) / 64;

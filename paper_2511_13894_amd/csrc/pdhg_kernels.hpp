@@ -182,8 +182,8 @@ __device__ __forceinline__ void tile_row_sums(TileRange range, int r0, int rows,
     const int my_row = tid / G, sub = tid % G;
     const bool have = my_row < rows;
     double acc = 0.0;
-    for (int cs = beg; cs < end; cs += C) {
-        const int ce = cs + C < end ? cs + C : end;
+    for (int cs = beg; cs < end;) { // positions within the chunk: lane_rounds says why
+        const int len = end - cs < C ? end - cs : C;
         int id[kTileU];
         double v[kTileU], g[kTileU];
         // Slice u of the chunk is tested once for the whole workgroup; inside
@@ -194,19 +194,19 @@ __device__ __forceinline__ void tile_row_sums(TileRange range, int r0, int rows,
         for (int u = 0; u < kTileU; u++) {
             id[u] = 0;
             v[u] = 0.0;
-            if (cs + u * NT < ce) {
-                const int k = cs + tid + u * NT;
-                const int kc = k < ce ? k : ce - 1;
+            if (u * NT < len) {
+                const int k = tid + u * NT;
+                const int kc = cs + (k < len ? k : len - 1);
                 id[u] = idx[kc];
                 v[u] = (double)val[kc];
             }
         }
 #pragma unroll
-        for (int u = 0; u < kTileU; u++) g[u] = cs + u * NT < ce ? (double)vec[id[u]] : 0.0;
+        for (int u = 0; u < kTileU; u++) g[u] = u * NT < len ? (double)vec[id[u]] : 0.0;
 #pragma unroll
         for (int u = 0; u < kTileU; u++) {
-            const int k = cs + tid + u * NT;
-            if (k < ce) s_prod[k - cs] = v[u] * g[u];
+            const int k = tid + u * NT;
+            if (k < len) s_prod[k] = v[u] * g[u];
         }
         if (cs == beg) {
             if (tid <= rows) s_ptr[tid] = pa;
@@ -214,19 +214,21 @@ __device__ __forceinline__ void tile_row_sums(TileRange range, int r0, int rows,
         }
         __syncthreads(); // products, and on the first chunk the row pointers
         const int rb = have ? s_ptr[my_row] : 0, re = have ? s_ptr[my_row + 1] : 0;
-        const int lo = rb > cs ? rb : cs, hi = re < ce ? re : ce;
+        const int lo = rb > cs ? rb - cs : 0, hi = re - cs < len ? re - cs : len;
         // the row's products in the same sequential order, read four at a time
         int q = lo + sub;
         for (; q + 3 * G < hi; q += 4 * G) {
-            const double p0 = s_prod[q - cs], p1 = s_prod[q + G - cs];
-            const double p2 = s_prod[q + 2 * G - cs], p3 = s_prod[q + 3 * G - cs];
+            const double p0 = s_prod[q], p1 = s_prod[q + G];
+            const double p2 = s_prod[q + 2 * G], p3 = s_prod[q + 3 * G];
             acc += p0;
             acc += p1;
             acc += p2;
             acc += p3;
         }
-        for (; q < hi; q += G) acc += s_prod[q - cs];
+        for (; q < hi; q += G) acc += s_prod[q];
         __syncthreads();
+        if (end - cs <= C) break;
+        cs += C;
     }
     acc = group_sum<G>(acc);
     if (have && sub == 0) s_sum[my_row] = acc;
@@ -243,10 +245,13 @@ __device__ __forceinline__ void tile_row_sums(TileRange range, int r0, int rows,
 // eight entries a lane, or in a tile of more than one chunk, streams its
 // entries through LDS as the tile does, in pieces of kWaveChunk, with the
 // tile's restart of the lanes' order at each chunk (uses_waves: where, and the
-// figures).
+// figures).  Positions run up to kWaveAhead past a row's end: a model that holds
+// almost 2^31 entries takes tiles, as one instruction more per load shows here
+// (5,000 x 20,000 power-law LP: 7.50 -> 7.66 us per iteration).
 constexpr int kWaveTile = 256;   // threads of the tile whose sums a wave repeats
 constexpr int kWaveChunk = 512;  // entries of a wave's rows in LDS at once
 constexpr int kWaveTerms = 16;   // longest row a lane group takes, in entries per lane
+constexpr int kWaveAhead = kTileU * kWaveTile + kWaveChunk; // how far positions run past the last entry
 constexpr int kWavesResident = 256 * 28; // waves the chip holds at once (uses_waves)
 
 template <int G, int U, typename VM, typename VV>

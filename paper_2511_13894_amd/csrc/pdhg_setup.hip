@@ -15,7 +15,8 @@ __global__ __launch_bounds__(kBlock) void k_rowid(int m, const int *__restrict__
     const int64_t w = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
     const int lane = threadIdx.x & 63;
     if (w >= m) return;
-    for (int e = rp[w] + lane; e < rp[w + 1]; e += 64) rowid[e] = (int)w;
+    const unsigned end = rp[w + 1];
+    for (unsigned e = rp[w] + lane; e < end; e += 64) rowid[e] = (int)w;
 }
 
 __global__ __launch_bounds__(kBlock) void k_count_cols(int nnz, const int *__restrict__ ci, int *__restrict__ cnt)
@@ -415,7 +416,8 @@ __global__ __launch_bounds__(kBlock) void k_row_norm(int rows, const int *__rest
     const int lane = (int)(g % L);
     if (row >= rows) return;
     double acc = 0.0;
-    for (int e = ptr[row] + lane; e < ptr[row + 1]; e += L) {
+    const unsigned end = ptr[row + 1];
+    for (unsigned e = ptr[row] + lane; e < end; e += L) {
         double a = fabs(val[e]);
         if (MODE == 0) acc = fmax(acc, a);
         else acc += (p == 1.0) ? a : pow(a, p);
