@@ -54,6 +54,7 @@ constexpr int kRowBlock = -2256; // kernel code: one row per workgroup of kBlock
 constexpr int kSell = -3032;     // kernel code (dual half): sliced ELLPACK, 32-row slices
 constexpr int kRowSegs = -4000;  // kernel code (dual half): row segments, each with its own lane-group width
 constexpr int kMaxRedBlocks = 1024; // cap on per-block partials of a reduction
+constexpr int64_t kMaxLaunchThreads = (int64_t)1 << 32; // a launch has fewer threads than this
 constexpr int kSegBlock = 64;       // workgroup of the row segments: one wave (see k_dual_segs)
 constexpr int kMaxSegs = 4;         // row segments of the kRowSegs dual half
 

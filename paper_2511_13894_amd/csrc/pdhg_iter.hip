@@ -1604,11 +1604,17 @@ hipError_t report(pdhg_solver *s, const double *x, const double *y, double *z, p
     hipStream_t st = s->stream;
     // both products, both parts, the sums: three launches in place of five, each a
     // launch's latency on a small LP (kkt of a 20,000 x 50,000 LP, with the copies
-    // of the point, 90-96 -> 65 us)
+    // of the point, 90-96 -> 65 us); past a billion entries the two products may
+    // need more threads than a launch can have, and each gets its own
     ProductJobs<double> p;
     p.add(s->m, s->rp, s->ci, s->av, x, s->ax, s->lanes_a, kBlock);
     p.add(s->n, s->tp, s->ti, s->atv, y, s->aty, s->lanes_at, kBlock);
-    if (p.blocks > 0) hipLaunchKernelGGL(k_lane_products, dim3(p.blocks), dim3(kBlock), 0, st, p);
+    if ((int64_t)p.blocks * kBlock >= kMaxLaunchThreads) {
+        spmv<double, double, double, double>(st, s->lanes_a, s->m, s->rp, s->ci, s->av, x, s->ax);
+        spmv<double, double, double, double>(st, s->lanes_at, s->n, s->tp, s->ti, s->atv, y, s->aty);
+    } else if (p.blocks > 0) {
+        hipLaunchKernelGGL(k_lane_products, dim3(p.blocks), dim3(kBlock), 0, st, p);
+    }
     const int gm = s->red_blocks_m, gn = s->red_blocks_n;
     double *pr = s->partials;
     double *pc = s->partials + (size_t)6 * gm;
