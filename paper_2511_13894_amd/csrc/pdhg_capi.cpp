@@ -128,10 +128,13 @@ int run_phase(pdhg_solver *s, int64_t iters, int mode, double t0)
             int64_t cycles = check && !timed ? resident_cycles_max(s, mode, len) : 0;
             if (cycles > 0) { // a small LP: several cycles in one launch, up to the target
                 cycles = std::min<int64_t>(cycles, 1 + (left - len) / K);
+                // the host looks at the state after this launch; with a time limit after `depth` cycles,
+                // as in a phase of launched halves, so that the limit stops it no later
+                if (s->p.time_limit > 0.0) cycles = std::min<int64_t>(cycles, depth - enq);
                 HIPCHK(resident_cycles(s, len, (int)cycles, mode));
                 s->t_host += (cycles - 1) * K;
                 s->next_check += (cycles - 1) * K;
-                enq = depth; // then look at the state
+                enq = s->p.time_limit > 0.0 ? enq + (int)cycles - 1 : depth;
             } else if (check && len == K && s->p.use_graph && !timed) {
                 HIPCHK(capture_cycle(s, K, mode));
                 HIPCHK(hipGraphLaunch(s->graph_exec, s->stream));
