@@ -113,13 +113,16 @@ typedef struct pdhg_params {
                               columns are contiguous or spread out, each with its own
                               lane-group width (the default for rows of more than 48
                               entries; a batch takes tiled kernels only);
-                              0 = chosen from the mean row length                      */
+                              0 = chosen from the mean row length; short rows in
+                              tiles of 32, 64 or 256 may then run as waves, lane
+                              groups of one-wave workgroups with the tiles' sums        */
     int32_t lanes_a;       /* dual-half kernel, same encoding                           */
     int32_t use_graph;     /* 1: replay check cycles from a captured hipGraph (default) */
     int32_t timing;        /* 1: time one primal and one dual launch per cycle with HIP
                               events on the solver's stream (read by pdhg_get_timing)  */
-    int32_t autotune;      /* 1: at create, time every kernel choice of each half on
-                              scratch vectors and keep the fastest (0 = default: the
+    int32_t autotune;      /* 1: at create, time every kernel choice of each half (such
+                              tiles also as waves) on scratch vectors and keep the
+                              fastest (0 = default: the
                               mean-row-length rule, reproducible run to run)          */
     int32_t record_history;/* 1: keep x and z of the last 4 restarts of the solve (the
                               learned push's trend features); default 0               */
@@ -214,7 +217,8 @@ typedef struct pdhg_timing {
                               ran on (the push may iterate on fewer columns); the
                               current model's count when nothing was sampled           */
     int64_t bytes_dual;    /* the same for the dual half                              */
-    int32_t lanes_at;      /* primal-half kernel in use (lanes_at encoding)           */
+    int32_t lanes_at;      /* primal-half kernel in use (lanes_at encoding; waves as
+                              the tiles whose sums they form)                         */
     int32_t lanes_a;       /* dual-half kernel in use                                  */
 } pdhg_timing;
 

@@ -6,8 +6,8 @@
 // DevState (step sizes, Halpern counter, restart state, done flag), its own
 // scaling, step size and checks; checks reduce per-tile partial sums of each
 // LP in a fixed order, so an LP's trajectory does not depend on the others.
-#include <climits>
 #include <cmath>
+#include <cstdio>
 
 #include <algorithm>
 #include <vector>
@@ -161,10 +161,9 @@ __global__ __launch_bounds__(64) void kb_dual_wave(const int4 *__restrict__ tile
 // 6.14 in the push; with the line at all the waves the push of 64 LPs of up
 // to 20,000 rows 17.2 -> 18.0 us, with no line that of 500-5,000 rows 17.0 ->
 // 19.5 (the LPs gather from short vectors, so tiles wait less).
-static bool batch_waves(const pdhg_batch *b, int kern, int tiles, bool dual)
+bool batch_waves(const pdhg_batch *b, int kern, int tiles, bool dual)
 {
-    if ((kern != -32 && kern != -64 && kern != -128 && kern != -256) || b->s->nnz > INT_MAX - kWaveAhead) return false;
-    if ((dual ? b->s->longest_row : b->s->longest_col) > kWaveTerms * (kWaveTile / -kern)) return false;
+    if ((dual ? b->s->waves_a : b->s->waves_at) == WAVES_NEVER || !waves_possible(b->s, kern, dual)) return false;
     return kTileWaves * (int64_t)tiles <= kWavesResident / 2;
 }
 
@@ -183,7 +182,6 @@ static void launch_primal_b(pdhg_batch *b, int i, int store, hipEvent_t e0 = nul
         switch (-b->kern_at) {
             PDHG_W_CASE(32, 8)
             PDHG_W_CASE(64, 4)
-            PDHG_W_CASE(128, 2)
         default:
             PDHG_W_CASE(256, 1)
         }
@@ -224,7 +222,6 @@ static void launch_dual_b(pdhg_batch *b, int i, int store, hipEvent_t e0 = nullp
         switch (-b->kern_a) {
             PDHG_W_CASE(32, 8)
             PDHG_W_CASE(64, 4)
-            PDHG_W_CASE(128, 2)
         default:
             PDHG_W_CASE(256, 1)
         }
@@ -468,7 +465,6 @@ static void launch_spmv_b(pdhg_batch *b, int kern, const int4 *tiles, int ntiles
         switch (-kern) {
             PDHG_W_CASE(32, 8)
             PDHG_W_CASE(64, 4)
-            PDHG_W_CASE(128, 2)
         default:
             PDHG_W_CASE(256, 1)
         }
@@ -1488,10 +1484,18 @@ hipError_t batch_autotune(pdhg_batch *b)
     s->yp = syp;
     int best_at = b->kern_at, best_a = b->kern_a;
     for (int half = 0; half < 2 && e == hipSuccess; half++) {
+        Waves &waves = half == 0 ? s->waves_at : s->waves_a;
+        Waves best_w = waves;
         float best = 1e30f;
-        for (int c : cands) {
+        // every candidate by the rule, and where that runs it as waves also as tiles
+        for (int k = 0; k < 2 * (int)(sizeof cands / sizeof cands[0]); k++) {
+            const int c = cands[k / 2];
+            waves = WAVES_BY_RULE;
             e = half == 0 ? batch_set_kernels(b, c, best_a) : batch_set_kernels(b, best_at, c);
             if (e != hipSuccess) break;
+            const bool as_waves = batch_waves(b, c, half == 0 ? b->n_ptiles : b->n_dtiles, half == 1);
+            if (k % 2 && !as_waves) continue;
+            if (k % 2) waves = WAVES_NEVER;
             for (int rep = 0; rep < 4; rep++) {
                 if (rep == 1) hipEventRecord(e0, s->stream);
                 if (half == 0) {
@@ -1507,12 +1511,17 @@ hipError_t batch_autotune(pdhg_batch *b)
             float ms = 0.0f;
             if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
             if (e != hipSuccess) break;
+            if (s->p.verbosity > 0)
+                fprintf(stderr, "[pdhg] autotune batch %s half: kernel %d%s %.2f us\n", half == 0 ? "primal" : "dual", c,
+                        as_waves && k % 2 == 0 ? " as waves" : "", ms / 3 * 1e3);
             if (ms < best) {
                 best = ms;
+                best_w = waves;
                 if (half == 0) best_at = c;
                 else best_a = c;
             }
         }
+        waves = best_w;
     }
     s->x = keep[0];
     s->xbar = keep[1];

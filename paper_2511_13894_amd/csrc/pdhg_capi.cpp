@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <cstdio>
 #include <cstring>
 #include <new>
 #include <numeric>
@@ -442,6 +443,8 @@ static int build_solver(int m, int n, int nz, const pdhg_params &p, const ModelS
         s->lanes_at = lanes_for_mean(mean_at);
         s->kern_a = p.lanes_a ? p.lanes_a : choose_kernel(mean_a, true);
         s->kern_at = p.lanes_at ? p.lanes_at : choose_kernel(mean_at, false);
+        s->waves_a = p.lanes_a ? WAVES_NEVER : WAVES_BY_RULE;
+        s->waves_at = p.lanes_at ? WAVES_NEVER : WAVES_BY_RULE;
         s->red_blocks_m = grid_for(m, kBlock, kMaxRedBlocks);
         s->red_blocks_n = grid_for(n, kBlock, kMaxRedBlocks);
         const size_t vb = s->fp32 ? sizeof(float) : sizeof(double);
@@ -554,6 +557,7 @@ static int build_solver(int m, int n, int nz, const pdhg_params &p, const ModelS
             HIPCHK(init_norms(s));
             HIPCHK(init_iteration(s));
             if (p.autotune) HIPCHK(autotune(s));
+            print_plan(s, "model");
         }
         HIPCHK(hipMemcpyAsync(s->st_host, s->st, sizeof(DevState), hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
@@ -1324,6 +1328,10 @@ static int batch_finish(pdhg_solver *s, int count, const std::vector<int> &roff,
         HIPCHK(batch_setup(b));
         HIPCHK(batch_phase_begin(b, true));
         if (p.autotune) HIPCHK(batch_autotune(b));
+        if (p.verbosity > 0)
+            fprintf(stderr, "[pdhg] batch of %d: primal half: kernel %d%s; dual half: kernel %d%s\n", count, b->kern_at,
+                    batch_waves(b, b->kern_at, b->n_ptiles, false) ? " as waves" : "", b->kern_a,
+                    batch_waves(b, b->kern_a, b->n_dtiles, true) ? " as waves" : "");
         HIPCHK(hipStreamSynchronize(st));
         b->t_host = 0;
         b->next_check = p.check_every;

@@ -389,7 +389,9 @@ hipError_t begin_impl(pdhg_solver *s)
     }
     if (s->kern_a == kRowSegs && (e = plan_row_segments(s)) != hipSuccess) return e; // of the compact rows
     if ((e = row_shapes(s)) != hipSuccess) return e; // of the compact model (on failure the caller restores the full one)
-    return resident_plan(s);
+    if ((e = resident_plan(s)) != hipSuccess) return e;
+    print_plan(s, "push on the free columns");
+    return hipSuccess;
 }
 
 template <typename V>

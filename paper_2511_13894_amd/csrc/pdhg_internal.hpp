@@ -69,6 +69,11 @@ struct RowSegs {
     int lanes[kMaxSegs] = {};
 };
 
+// Whether the tiles of a half run as waves (the same sums): where the library
+// chose the kernel, by the rules of uses_waves and batch_waves; never where the
+// caller named the tile; where it was timed at create, as it was faster.
+enum Waves : int8_t { WAVES_BY_RULE, WAVES_NEVER, WAVES_ALWAYS };
+
 // Quantities reduced at a check (block partials, then one fixed-order pass).
 enum CheckQ {
     Q_PH2 = 0, // sum rP_hat^2           (scaled, current senses)
@@ -186,6 +191,7 @@ struct pdhg_solver {
     int longest_col = 0, longest_row = 0; // entries of the longest column and row of the current model
     int beside = 0;                // entries of its rows that gather next to the row before them (row_shapes)
     int kern_at = 1, kern_a = 1;   // iteration kernels: > 0 lane-group width, < 0 LDS tile of -k rows
+    pdhg::Waves waves_at = pdhg::WAVES_BY_RULE, waves_a = pdhg::WAVES_BY_RULE; // whether tiles run as waves
     pdhg::RowSegs segs;            // the dual half's row segments (kern_a == kRowSegs)
     // a small LP's iterations in one workgroup: kernel variant (0: none), the
     // longest column, and the dual half's rounds of rows (first, past the last,
@@ -370,7 +376,9 @@ hipError_t defect_refresh(pdhg_solver *s);
 // udeg_at (the common entry count of every column, 1..3, or 0), longest_col,
 // longest_row and beside of the current model
 hipError_t row_shapes(pdhg_solver *s);
-bool uses_waves(const pdhg_solver *s, int kern, bool dual); // the tiles of `kern` run as waves
+bool waves_possible(const pdhg_solver *s, int kern, bool dual); // the tiles of `kern` may run as waves
+bool uses_waves(const pdhg_solver *s, int kern, bool dual);     // ... and do
+void print_plan(const pdhg_solver *s, const char *model); // verbosity > 0: the kernels of the current model, on stderr
 // the primal half runs the uniform-column kernel: columns of 1-3 entries each,
 // 256-row tiles chosen by the library (an explicit lanes_at keeps the tiles)
 inline bool uses_uniform_kernel(const pdhg_solver *s)
@@ -440,6 +448,7 @@ hipError_t batch_setup(pdhg_batch *b);
 hipError_t batch_autotune(pdhg_batch *b);
 hipError_t batch_compact_tiles(pdhg_batch *b, bool all, const double *done = nullptr);
 hipError_t batch_set_kernels(pdhg_batch *b, int kern_at, int kern_a);
+bool batch_waves(const pdhg_batch *b, int kern, int tiles, bool dual); // a launch over `tiles` tiles runs them as waves
 hipError_t batch_phase_begin(pdhg_batch *b, bool fresh);
 hipError_t batch_defect_refresh(pdhg_batch *b);
 hipError_t batch_iterations(pdhg_batch *b, int count, bool check_at_end, int mode, bool timed);

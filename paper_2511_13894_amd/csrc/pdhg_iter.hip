@@ -215,6 +215,12 @@ __device__ __forceinline__ double row_block_sum(int beg, int end, const int *__r
     return q[0];
 }
 
+bool waves_possible(const pdhg_solver *s, int kern, bool dual)
+{
+    if ((kern != -32 && kern != -64 && kern != -256) || s->nnz > INT_MAX - kWaveAhead) return false;
+    return (dual ? s->longest_row : s->longest_col) <= kWaveTerms * (kWaveTile / -kern);
+}
+
 // Whether the tiles of `kern` run as waves (wave_row_sum; the same bits).
 // A wave's lanes go straight from index to operand to sum, where a tile's
 // products pass through LDS behind two barriers, so a wave is done sooner; a
@@ -243,9 +249,10 @@ __device__ __forceinline__ double row_block_sum(int beg, int end, const int *__r
 // 111.0); where neither is, too: 128,000 rows 24.8 -> 25.4 (22.6 -> 22.9).
 bool uses_waves(const pdhg_solver *s, int kern, bool dual)
 {
-    if ((kern != -32 && kern != -64 && kern != -128 && kern != -256) || s->nnz > INT_MAX - kWaveAhead) return false;
+    if (!waves_possible(s, kern, dual)) return false;
+    const Waves how = dual ? s->waves_a : s->waves_at;
+    if (how != WAVES_BY_RULE) return how == WAVES_ALWAYS;
     const int G = kWaveTile / -kern;
-    if ((dual ? s->longest_row : s->longest_col) > kWaveTerms * G) return false;
     const int64_t waves = ((int64_t)(dual ? s->m : s->n) * G + 63) / 64;
     const bool dealt = waves >= kXcdChunkMin && (s->m - kern - 1) / -kern < kXcdChunkMin; // waves, but not tiles
     return waves <= kWavesResident || (dual && dealt && 4 * (int64_t)s->beside >= s->nnz);
@@ -339,7 +346,6 @@ static void check_spmv(hipStream_t st, int kern, bool waves, int rows, const int
         switch (T) {
             PDHG_W_CASE(32, 8)
             PDHG_W_CASE(64, 4)
-            PDHG_W_CASE(128, 2)
         default:
             PDHG_W_CASE(256, 1)
         }
@@ -444,7 +450,6 @@ __global__ __launch_bounds__(64) void k_wave_products(ProductJobs<VM> p)
     switch (p.job[k].lanes) {
     case 8: wave_product<VM, 8>(p.job[k], block, s_prod); break;
     case 4: wave_product<VM, 4>(p.job[k], block, s_prod); break;
-    case 2: wave_product<VM, 2>(p.job[k], block, s_prod); break;
     default: wave_product<VM, 1>(p.job[k], block, s_prod);
     }
 }
@@ -731,7 +736,6 @@ static void launch_primal(pdhg_solver *s, int i, int store, hipEvent_t e0 = null
         switch (-L) {
             PDHG_W_CASE(32, 8)
             PDHG_W_CASE(64, 4)
-            PDHG_W_CASE(128, 2)
         default:
             PDHG_W_CASE(256, 1)
         }
@@ -814,7 +818,6 @@ static void launch_dual(pdhg_solver *s, int i, int store, hipEvent_t e0 = nullpt
         switch (-L) {
             PDHG_W_CASE(32, 8)
             PDHG_W_CASE(64, 4)
-            PDHG_W_CASE(128, 2)
         default:
             PDHG_W_CASE(256, 1)
         }
@@ -1153,6 +1156,7 @@ hipError_t row_shapes(pdhg_solver *s)
     s->udeg_at = s->longest_col = s->longest_row = s->beside = 0;
     if (s->n <= 0 || s->m <= 0) return hipSuccess;
     const int D = s->nnz % s->n == 0 ? s->nnz / s->n : 0;
+    // the lanes of the kernel that the rule of uses_waves is asked about: it decides only where kern_a is the library's choice
     const int G = s->kern_a < 0 && s->kern_a >= -kWaveTile ? kWaveTile / -s->kern_a : 64;
     int *d = (int *)s->redout, h[4] = {1, 0, 0, 0}; // small scratch of the handle, free outside a check
     hipLaunchKernelGGL(k_zero_shapes, dim3(1), dim3(4), 0, s->stream, d);
@@ -1971,6 +1975,18 @@ hipError_t plan_row_segments(pdhg_solver *s)
     return hipSuccess;
 }
 
+void print_plan(const pdhg_solver *s, const char *model)
+{
+    if (s->p.verbosity <= 0) return;
+    fprintf(stderr, "[pdhg] %s: %d x %d, %d entries; primal half: kernel %d%s; dual half: kernel %d%s; ", model, s->m, s->n,
+            s->nnz, s->kern_at, uses_uniform_kernel(s) ? " for uniform columns" : uses_waves(s, s->kern_at, false) ? " as waves" : "",
+            s->kern_a, uses_waves(s, s->kern_a, true) ? " as waves" : "");
+    if (s->res.variant > 0)
+        fprintf(stderr, "in one workgroup, variant %d, %d row rounds%s\n", s->res.variant, s->res.rounds,
+                s->res.fma ? " of lane groups" : "");
+    else fprintf(stderr, "launched\n");
+}
+
 // Time every candidate of each half on scratch output vectors (3 launches
 // each after one warm-up) and keep the fastest.  The iterate is untouched.
 hipError_t autotune(pdhg_solver *s)
@@ -1996,13 +2012,19 @@ hipError_t autotune(pdhg_solver *s)
     s->y = sy;
     s->yp = syp;
     for (int half = 0; half < 2 && e == hipSuccess; half++) {
+        int &kern = half == 0 ? s->kern_at : s->kern_a;
+        Waves &waves = half == 0 ? s->waves_at : s->waves_a;
         float best = 1e30f;
-        int best_k = half == 0 ? s->kern_at : s->kern_a;
-        for (int c : cands) {
+        int best_k = kern;
+        Waves best_w = waves;
+        // every candidate, tiles also as waves
+        for (int k = 0; k < 2 * (int)(sizeof cands / sizeof cands[0]); k++) {
+            const int c = cands[k / 2];
             if (c == kSell && (half == 0 || !s->sell_idx)) continue; // dual half, layout built
             if (c == kRowSegs && (half == 0 || s->segs.count == 0)) continue; // dual half, segments planned
-            if (half == 0) s->kern_at = c;
-            else s->kern_a = c;
+            kern = c;
+            waves = k % 2 ? WAVES_ALWAYS : WAVES_NEVER;
+            if (k % 2 && (!waves_possible(s, c, half == 1) || (half == 0 && uses_uniform_kernel(s)))) continue;
             for (int rep = 0; rep < 4; rep++) {
                 if (rep == 1) hipEventRecord(e0, s->stream);
                 if (half == 0) {
@@ -2018,13 +2040,17 @@ hipError_t autotune(pdhg_solver *s)
             float ms = 0.0f;
             if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
             if (e != hipSuccess) break;
+            if (s->p.verbosity > 0)
+                fprintf(stderr, "[pdhg] autotune %s half: kernel %d%s %.2f us\n", half == 0 ? "primal" : "dual", c,
+                        k % 2 ? " as waves" : "", ms / 3 * 1e3);
             if (ms < best) {
                 best = ms;
                 best_k = c;
+                best_w = waves;
             }
         }
-        if (half == 0) s->kern_at = best_k;
-        else s->kern_a = best_k;
+        kern = best_k;
+        waves = best_w;
     }
     s->x = keep[0];
     s->xbar = keep[1];
