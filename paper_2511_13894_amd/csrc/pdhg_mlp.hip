@@ -107,7 +107,8 @@ __device__ __forceinline__ bf16x4 load_features(const float *__restrict__ F, int
 // weights, which every wave reads: 32 loads of 16 lines each, more of the CU's
 // cache than the features and the arithmetic of a tile (forward_grid).  65,536
 // variables, host calls included: 11.9 us per call with a separate bfloat16
-// pass and 2-byte weight loads, 9.1-11.2 with one tile a wave, 6.4 with four.
+// pass and 2-byte weight loads, 9.1-11.2 with one tile a wave, 6.4 with four, on
+// the same features again; on features that come from HBM 15.1 -> 7.5.
 template <typename FT>
 __global__ __launch_bounds__(kBlock) void k_mlp_forward(const FT *__restrict__ F, int64_t N, MlpW w,
                                                        float *__restrict__ logits)
@@ -504,15 +505,17 @@ hipError_t mlp_init(pdhg_mlp *net, uint64_t seed)
     hipLaunchKernelGGL(k_mlp_init, dim3((MLP_NPARAMS + kBlock - 1) / kBlock), dim3(kBlock), 0, net->stream, net->p, net->m,
                        net->v, seed);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return mlp_sync(net);
+    if (e == hipSuccess) e = hipStreamSynchronize(net->stream);
+    // on the pass stream, so that its first launch, which sets it up, is not a caller's
+    if (e == hipSuccess) e = mlp_sync(net, net->pass);
+    return e == hipSuccess ? hipStreamSynchronize(net->pass) : e;
 }
 
 static MlpW weights(const pdhg_mlp *net) { return MlpW{net->w1b, net->w2b, net->w3b, net->w2tb, net->p}; }
 
-hipError_t mlp_sync(pdhg_mlp *net)
+hipError_t mlp_sync(pdhg_mlp *net, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_mlp_sync_bf16, dim3((MLP_NPARAMS + kBlock - 1) / kBlock), dim3(kBlock), 0, net->stream, net->p,
+    hipLaunchKernelGGL(k_mlp_sync_bf16, dim3((MLP_NPARAMS + kBlock - 1) / kBlock), dim3(kBlock), 0, st, net->p,
                        net->w1b, net->w2b, net->w3b, net->w2tb);
     return hipGetLastError();
 }
@@ -526,7 +529,7 @@ hipError_t mlp_features_to_bf16(hipStream_t st, const float *src, short *dst, in
 // Workgroups of a forward pass: one tile a wave until every CU has a workgroup,
 // then as many tiles a wave as keep it at one, at most 8 (16 past a million
 // variables, where the chain of a wave's tiles hides behind the other waves).
-// us by rocprofv3, one tile a wave -> this rule: 65,536 variables 11.4 -> 6.0,
+// us by rocprofv3 on the same features again, one tile a wave -> this rule: 65,536 variables 11.4 -> 6.0,
 // 131,072 20.8 -> 8.9 (9.2 with 4 tiles, 13.5 with 16), 262,144 39.8 -> 13.0
 // (15.1, 14.3), 1,048,576 152 -> 34 (38 with 8), 4,194,304 598 -> 108 (126).
 static int forward_grid(int64_t tiles)

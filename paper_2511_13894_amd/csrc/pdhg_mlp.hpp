@@ -25,7 +25,7 @@ struct pdhg_mlp {
 };
 
 namespace pdhg {
-hipError_t mlp_sync(pdhg_mlp *net);
+hipError_t mlp_sync(pdhg_mlp *net, hipStream_t st); // the bfloat16 copies of the weights
 hipError_t mlp_init(pdhg_mlp *net, uint64_t seed);
 hipError_t mlp_features_to_bf16(hipStream_t st, const float *src, short *dst, int64_t n_rows);
 hipError_t mlp_forward(const pdhg_mlp *net, hipStream_t st, const short *F, int64_t N, float *logits);

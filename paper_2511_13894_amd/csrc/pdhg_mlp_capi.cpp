@@ -131,7 +131,7 @@ int pdhg_mlp_set_params(pdhg_mlp *net, const float *params)
         CHK(hipMemsetAsync(net->m, 0, sizeof(float) * MLP_NPARAMS, net->stream));
         CHK(hipMemsetAsync(net->v, 0, sizeof(float) * MLP_NPARAMS, net->stream));
         net->adam_t = 0;
-        CHK(mlp_sync(net));
+        CHK(mlp_sync(net, net->stream));
         CHK(hipStreamSynchronize(net->stream));
     } catch (const HipFail &f) {
         return hip_fail(f);
