@@ -478,7 +478,9 @@ int pdhg_mlp_forward(pdhg_mlp *net, const float *features, int64_t n, float *log
  * logits[n] are the caller's device buffers, on the device the network was
  * created on; the work is enqueued on `stream` (a hipStream_t, NULL: one of
  * the library's, on which the passes of a device's networks run in the order
- * of their calls) and the call returns without waiting.  n is at most
+ * of their calls; one that another thread calls during a pdhg_mlp_train or
+ * pdhg_mlp_set_params of the network sees the weights between two steps, or
+ * before or after they are set) and the call returns without waiting.  n is at most
  * 65536 per call (INVALID_ARG beyond); no allocation, no synchronisation.
  * Where logits overlaps features, a bfloat16 copy of the features is staged
  * in a fixed 2 MiB device array per GPU, which such calls share: those that

@@ -639,7 +639,9 @@ hipError_t mlp_scratch_setup() // at pdhg_mlp_create, on the device the network 
 // writes to the next network's pass.  The networks of a device share one stream
 // for them, made with the first and given back with the last (a stream per
 // network with events between them measured 21 us per call by turns, one
-// stream 5.6).  What changes a network's weights waits for its passes first.
+// stream 5.6).  What changes a network's weights waits for its passes first; while
+// another thread trains the network its passes are enqueued on the network's own
+// stream instead, between two steps, and ordered with the shared one by events.
 namespace {
 struct PassStream {
     hipStream_t st = nullptr;
@@ -658,6 +660,8 @@ hipError_t mlp_pass_open(pdhg_mlp *net)
     std::lock_guard<std::mutex> lock(g_pass_mu);
     PassStream &p = g_pass[dev];
     if (!p.st && (e = hipStreamCreate(&p.st)) != hipSuccess) return e;
+    for (hipEvent_t &v : net->order)
+        if ((e = hipEventCreateWithFlags(&v, hipEventDisableTiming)) != hipSuccess) return e;
     p.users++;
     net->device = dev;
     net->pass = p.st;
@@ -666,6 +670,8 @@ hipError_t mlp_pass_open(pdhg_mlp *net)
 
 void mlp_pass_close(pdhg_mlp *net)
 {
+    for (hipEvent_t &v : net->order)
+        if (v) (void)hipEventDestroy(v);
     if (!net->pass) return;
     std::lock_guard<std::mutex> lock(g_pass_mu);
     PassStream &p = g_pass[net->device];
@@ -677,8 +683,24 @@ void mlp_pass_close(pdhg_mlp *net)
 
 hipError_t mlp_pass_wait(pdhg_mlp *net)
 {
-    return net->pass && net->passed.exchange(false) ? hipStreamSynchronize(net->pass) : hipSuccess;
+    if (!net->pass || !net->passed) return hipSuccess;
+    net->passed = false;
+    return hipStreamSynchronize(net->pass);
 }
+
+namespace {
+// the pass itself: features and logits on the current device
+hipError_t enqueue_pass(pdhg_mlp *net, hipStream_t st, const float *features, int64_t n, float *logits)
+{
+    const uintptr_t f0 = (uintptr_t)features, f1 = (uintptr_t)(features + 16 * n), l0 = (uintptr_t)logits,
+                    l1 = (uintptr_t)(logits + n);
+    if (l0 >= f1 || f0 >= l1) return forward_impl(net, st, features, n, logits);
+    short *fb = nullptr;
+    hipError_t e = scratch_for_current_device(&fb);
+    if (e == hipSuccess) e = mlp_features_to_bf16(st, features, fb, n); // every staged row is overwritten: nothing to clear
+    return e == hipSuccess ? mlp_forward(net, st, fb, n, logits) : e;
+}
+} // namespace
 
 } // namespace pdhg
 
@@ -690,21 +712,23 @@ extern "C" int pdhg_mlp_forward_noalloc(pdhg_mlp *net, const float *features, in
     if (n > kNoAllocMaxRows)
         return fail(PDHG_ERR_INVALID_ARG, "pdhg_mlp_forward_noalloc takes at most 65536 variables per call");
     if (n == 0) return PDHG_OK;
-    hipStream_t st = stream ? (hipStream_t)stream : net->pass;
-    const uintptr_t f0 = (uintptr_t)features, f1 = (uintptr_t)(features + 16 * n), l0 = (uintptr_t)logits,
-                    l1 = (uintptr_t)(logits + n);
-    if (!stream) net->passed = true;
     hipError_t e = hipSuccess;
-    if (l0 >= f1 || f0 >= l1) {
-        e = forward_impl(net, st, features, n, logits);
+    if (stream) {
+        e = enqueue_pass(net, (hipStream_t)stream, features, n, logits);
     } else {
-        short *fb = nullptr;
-        e = scratch_for_current_device(&fb);
-        if (e != hipSuccess)
-            return fail(PDHG_ERR_HIP, std::string("HIP error in hipGetSymbolAddress: ") + hipGetErrorString(e));
-        e = mlp_features_to_bf16(st, features, fb, n); // every staged row is overwritten: nothing to clear
-        if (e == hipSuccess) e = mlp_forward(net, st, fb, n, logits);
+        std::lock_guard<std::mutex> lock(net->mu);
+        const bool beside = net->training > 0;
+        if (beside) {
+            e = hipEventRecord(net->order[0], net->pass);
+            if (e == hipSuccess) e = hipStreamWaitEvent(net->stream, net->order[0], 0);
+        }
+        if (e == hipSuccess) e = enqueue_pass(net, beside ? net->stream : net->pass, features, n, logits);
+        if (beside && e == hipSuccess) {
+            e = hipEventRecord(net->order[1], net->stream);
+            if (e == hipSuccess) e = hipStreamWaitEvent(net->pass, net->order[1], 0);
+        }
+        net->passed = true;
     }
-    if (e != hipSuccess) return fail(PDHG_ERR_HIP, std::string("HIP error in the forward launch: ") + hipGetErrorString(e));
+    if (e != hipSuccess) return fail(PDHG_ERR_HIP, std::string("HIP error in the forward pass: ") + hipGetErrorString(e));
     return PDHG_OK;
 }

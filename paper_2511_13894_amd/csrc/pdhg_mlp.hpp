@@ -3,8 +3,8 @@
 
 #include <hip/hip_runtime.h>
 
-#include <atomic>
 #include <cstdint>
+#include <mutex>
 
 #include "pdhg.h"
 
@@ -21,7 +21,10 @@ struct pdhg_mlp {
     int64_t adam_t = 0;
     int device = -1;
     hipStream_t pass = nullptr; // forward passes of callers who name no stream: one stream for a device's networks
-    std::atomic<bool> passed{false}; // such passes may be in flight
+    std::mutex mu;              // held while such a pass is enqueued and while it is decided where they run:
+    bool passed = false;        // passes may be in flight on `pass`
+    int training = 0;           // calls that train on `stream`: passes are enqueued there, between their steps
+    hipEvent_t order[2] = {nullptr, nullptr}; // such a pass after those on `pass`, and the next ones after it
 };
 
 namespace pdhg {
@@ -36,7 +39,7 @@ hipError_t mlp_train_step(pdhg_mlp *net, const short *F, const float *Y, const i
 // device address of the no-allocation forward's staging array on the current
 // device (looked up once per device)
 hipError_t mlp_scratch_setup();
-// take and give back the device's shared pass stream; wait for the passes on it
+// take and give back the device's shared pass stream; wait for the passes on it (net->mu held)
 hipError_t mlp_pass_open(pdhg_mlp *net);
 void mlp_pass_close(pdhg_mlp *net);
 hipError_t mlp_pass_wait(pdhg_mlp *net);

@@ -63,6 +63,30 @@ struct DevSet {
     }
 };
 
+// wait for the passes that name no stream, as for all work on the network's own one
+void wait_for_passes(pdhg_mlp *net)
+{
+    std::lock_guard<std::mutex> lock(net->mu);
+    CHK(mlp_pass_wait(net));
+}
+
+// While this lives the network's weights change on its own stream, and passes run between the changes.
+struct Training {
+    pdhg_mlp *net;
+    explicit Training(pdhg_mlp *q) : net(q)
+    {
+        std::lock_guard<std::mutex> lock(net->mu);
+        CHK(mlp_pass_wait(net));
+        net->training++;
+    }
+    ~Training()
+    {
+        std::lock_guard<std::mutex> lock(net->mu);
+        (void)hipStreamSynchronize(net->stream); // also passes enqueued beside the last steps
+        net->training--;
+    }
+};
+
 void upload(pdhg_mlp *net, DevSet &d, const float *features, const float *labels, int64_t n)
 {
     CHK(hipMalloc(&d.F, sizeof(short) * 16 * (size_t)n));
@@ -112,7 +136,7 @@ int pdhg_mlp_create(uint64_t seed, pdhg_mlp **out)
 void pdhg_mlp_destroy(pdhg_mlp *net)
 {
     if (!net) return;
-    (void)mlp_pass_wait(net);
+    (void)mlp_pass_wait(net); // no other call may be under way
     if (net->stream) (void)hipStreamSynchronize(net->stream);
     mlp_pass_close(net);
     for (void *q : {(void *)net->p, (void *)net->m, (void *)net->v, (void *)net->grad, (void *)net->w1b,
@@ -126,7 +150,8 @@ int pdhg_mlp_set_params(pdhg_mlp *net, const float *params)
 {
     if (!net || !params) return fail(PDHG_ERR_INVALID_ARG, "NULL argument");
     try {
-        CHK(mlp_pass_wait(net)); // they still read the weights
+        std::lock_guard<std::mutex> lock(net->mu); // no pass sees some of the new weights
+        CHK(mlp_pass_wait(net));
         CHK(hipMemcpyAsync(net->p, params, sizeof(float) * MLP_NPARAMS, hipMemcpyHostToDevice, net->stream));
         CHK(hipMemsetAsync(net->m, 0, sizeof(float) * MLP_NPARAMS, net->stream));
         CHK(hipMemsetAsync(net->v, 0, sizeof(float) * MLP_NPARAMS, net->stream));
@@ -143,7 +168,7 @@ int pdhg_mlp_get_params(pdhg_mlp *net, float *params)
 {
     if (!net || !params) return fail(PDHG_ERR_INVALID_ARG, "NULL argument");
     try {
-        CHK(mlp_pass_wait(net));
+        wait_for_passes(net);
         CHK(hipMemcpyAsync(params, net->p, sizeof(float) * MLP_NPARAMS, hipMemcpyDeviceToHost, net->stream));
         CHK(hipStreamSynchronize(net->stream));
     } catch (const HipFail &f) {
@@ -157,7 +182,7 @@ int pdhg_mlp_forward(pdhg_mlp *net, const float *features, int64_t n, float *log
     if (!net || (n > 0 && (!features || !logits)) || n < 0) return fail(PDHG_ERR_INVALID_ARG, "bad arguments");
     if (n == 0) return PDHG_OK;
     try {
-        CHK(mlp_pass_wait(net));
+        wait_for_passes(net);
         DevSet d;
         upload(net, d, features, nullptr, n);
         float *dl = nullptr;
@@ -179,7 +204,7 @@ int pdhg_mlp_gradient(pdhg_mlp *net, const float *features, const float *labels,
     if (!net || !features || !labels || !grad || n < 1 || n > kMaxBatch)
         return fail(PDHG_ERR_INVALID_ARG, "bad arguments (1 <= n <= 65536)");
     try {
-        CHK(mlp_pass_wait(net));
+        wait_for_passes(net);
         DevSet d;
         upload(net, d, features, labels, n);
         std::vector<int> idx((size_t)n);
@@ -223,7 +248,7 @@ int pdhg_mlp_train(pdhg_mlp *net, const float *features, const float *labels, in
     if (t.batch < 1 || t.batch > kMaxBatch || t.epochs < 0) return fail(PDHG_ERR_INVALID_ARG, "bad training parameters");
     const double t0 = now_s();
     try {
-        CHK(mlp_pass_wait(net));
+        Training training(net);
         // positive-class weight N_neg / N_pos unless given
         double pw = t.pos_weight;
         if (!(pw > 0.0)) {
