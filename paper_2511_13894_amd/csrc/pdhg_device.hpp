@@ -186,6 +186,41 @@ __device__ __forceinline__ ACC lane_rounds(int beg, int end, int lane, const I *
     }
 }
 
+// The same in rounds of four and a last one of up to three entries, one after
+// another: fewer instructions than the rounds above.
+template <int L, typename ACC, typename I, typename VM, typename VX>
+__device__ __forceinline__ ACC lane_short(int beg, int end, int lane, const I *__restrict__ idx,
+                                          const VM *__restrict__ val, const VX *__restrict__ x)
+{
+    ACC acc = 0;
+    int left = end - beg - lane;
+    for (; left > 3 * L; left -= 4 * L) {
+        const int e = end - left;
+        I i[4];
+        VM v[4];
+        VX g[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            i[u] = idx[e + u * L];
+            v[u] = val[e + u * L];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; u++) g[u] = x[i[u]];
+#pragma unroll
+        for (int u = 0; u < 4; u++) acc += (ACC)v[u] * (ACC)g[u];
+    }
+    if (left > 0) {
+        const int e = end - left, c1 = L < left ? e + L : e, c2 = 2 * L < left ? e + 2 * L : e;
+        const I i0 = idx[e], i1 = idx[c1], i2 = idx[c2];
+        const ACC v0 = (ACC)val[e], v1 = (ACC)val[c1], v2 = (ACC)val[c2];
+        const ACC g0 = (ACC)x[i0], g1 = (ACC)x[i1], g2 = (ACC)x[i2];
+        acc += v0 * g0;
+        if (L < left) acc += v1 * g1;
+        if (2 * L < left) acc += v2 * g2;
+    }
+    return acc;
+}
+
 // Rounds of eight where a row of the wave has more than four entries a lane:
 // fewer waits in a chain; at most four entries: rounds of four, as the other
 // four loads would repeat the last entry.  Per iteration on transportation
@@ -193,11 +228,20 @@ __device__ __forceinline__ ACC lane_rounds(int beg, int end, int lane, const I *
 // / 6.55 us, 1000x2500 46.8 / 35.6 -> 46.9 / 33.6; 2000x5000 228.7 / 159.2 ->
 // 225.8 / 158.9 in the solve, 16.3 / 12.8 -> 16.2 / 12.6 in the push (12.9
 // with rounds of eight alone: its sink rows have three entries a lane).
+// Where no row has more than one entry a lane, one round of one, as the other
+// three would fetch the row's last entry: planted 3,000 x 8,000 (5 and 13
+// entries) with 64 lanes 10.3 / 9.0 -> 8.7 / 8.4 us.  Lanes with rows of their
+// own, or two a row, end in different rounds wherever a row of the wave is
+// short, and instructions count: there one round after another, 3,000 x 8,000
+// with one lane 11.5 / 10.3 -> 9.7 / 8.7, power-law 2,000 x 8,000 28.7 / 26.5 ->
+// 22.2 / 21.0; rows of 150 and 225 entries keep the rounds (56.8 against 63).
 template <int L, typename ACC, typename I, typename VM, typename VX>
 __device__ __forceinline__ ACC lane_dot(int beg, int end, int lane, const I *__restrict__ idx,
                                         const VM *__restrict__ val, const VX *__restrict__ x)
 {
+    if (L <= 2 && __builtin_amdgcn_ballot_w64(end - beg <= 32 * L)) return lane_short<L, ACC>(beg, end, lane, idx, val, x);
     if (__builtin_amdgcn_ballot_w64(end - beg > 4 * L)) return lane_rounds<L, 8, ACC>(beg, end, lane, idx, val, x);
+    if (L >= 16 && !__builtin_amdgcn_ballot_w64(end - beg > L)) return lane_rounds<L, 1, ACC>(beg, end, lane, idx, val, x);
     return lane_rounds<L, 4, ACC>(beg, end, lane, idx, val, x);
 }
 

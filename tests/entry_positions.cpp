@@ -70,7 +70,7 @@ void expect(const char *what, int64_t len, double got, double want)
 template <int L>
 void lane_groups()
 {
-    for (int64_t len : {0, 1, L, 4 * L - 1, 4 * L, 4 * L + 1, 8 * L, 8 * L + 1, 17 * L + 3}) {
+    for (int64_t len : {0, 1, L, 4 * L - 1, 4 * L, 4 * L + 1, 8 * L, 8 * L + 1, 17 * L + 3, 41 * L}) {
         const int64_t beg = kEnd - len;
         double s = 0.0;
         for (int lane = 0; lane < L; lane++) s += pdhg::lane_dot<L, double>((int)beg, (int)kEnd, lane, idx, val, x);
