@@ -639,9 +639,9 @@ hipError_t mlp_scratch_setup() // at pdhg_mlp_create, on the device the network 
 // writes to the next network's pass.  The networks of a device share one stream
 // for them, made with the first and given back with the last (a stream per
 // network with events between them measured 21 us per call by turns, one
-// stream 5.6).  What changes a network's weights waits for its passes first; while
-// another thread trains the network its passes are enqueued on the network's own
-// stream instead, between two steps, and ordered with the shared one by events.
+// stream 5.6).  What works on a network's own stream waits for its passes first;
+// those that another thread calls meanwhile are enqueued on that stream, between
+// a training's steps, and ordered with the shared one by events.
 namespace {
 struct PassStream {
     hipStream_t st = nullptr;
@@ -717,7 +717,7 @@ extern "C" int pdhg_mlp_forward_noalloc(pdhg_mlp *net, const float *features, in
         e = enqueue_pass(net, (hipStream_t)stream, features, n, logits);
     } else {
         std::lock_guard<std::mutex> lock(net->mu);
-        const bool beside = net->training > 0;
+        const bool beside = net->busy > 0;
         if (beside) {
             e = hipEventRecord(net->order[0], net->pass);
             if (e == hipSuccess) e = hipStreamWaitEvent(net->stream, net->order[0], 0);
@@ -728,6 +728,7 @@ extern "C" int pdhg_mlp_forward_noalloc(pdhg_mlp *net, const float *features, in
             if (e == hipSuccess) e = hipStreamWaitEvent(net->pass, net->order[1], 0);
         }
         net->passed = true;
+        net->beside = net->beside || beside;
     }
     if (e != hipSuccess) return fail(PDHG_ERR_HIP, std::string("HIP error in the forward pass: ") + hipGetErrorString(e));
     return PDHG_OK;

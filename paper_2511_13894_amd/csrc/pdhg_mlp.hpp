@@ -23,7 +23,8 @@ struct pdhg_mlp {
     hipStream_t pass = nullptr; // forward passes of callers who name no stream: one stream for a device's networks
     std::mutex mu;              // held while such a pass is enqueued and while it is decided where they run:
     bool passed = false;        // passes may be in flight on `pass`
-    int training = 0;           // calls that train on `stream`: passes are enqueued there, between their steps
+    int busy = 0;               // calls that work on `stream`: passes are enqueued there, between a training's steps
+    bool beside = false;        // and some have been
     hipEvent_t order[2] = {nullptr, nullptr}; // such a pass after those on `pass`, and the next ones after it
 };
 
