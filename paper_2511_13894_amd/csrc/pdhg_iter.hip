@@ -1021,24 +1021,20 @@ __global__ __launch_bounds__(kBlock) void k_restart_apply(int n, int m, const De
     }
 }
 
-// Anchored objective and right-hand side (mixed mode): chc = ch - (pa + pb)
-// and bhc = bh - (qa + qb), where pa + pb = E' y_a and qa + qb = Ahat x_a in
-// float64 (pb, qb may be NULL; qa may be the output itself).  At a restart the
-// candidate becomes the anchor and the check has just left E' y+ in ety and
-// the float64 product Ahat x+ in ax; with `always` (a phase start)
-// regardless of the restart flag.
-__global__ __launch_bounds__(kBlock) void k_defect_set(int n, int m, const DevState *st, int always,
-                                                      const double *ch, const double *pa, const double *pb,
-                                                      double *chc, const double *bh, const double *qa,
-                                                      const double *qb, double *bhc)
+// Anchored objective and right-hand side at a phase start (mixed mode):
+// chc = ch - E' y_a from ety, and bhc = bh - Ahat x_a, with fl32(Ahat) x_a in bhc
+// and E x_a in ex.  (A restart's are set by k_restart_apply.)
+__global__ __launch_bounds__(kBlock) void k_defect_set(int n, int m, const double *__restrict__ ch,
+                                                      const double *__restrict__ ety, double *__restrict__ chc,
+                                                      const double *__restrict__ bh, const double *__restrict__ ex,
+                                                      double *__restrict__ bhc)
 {
-    if (!always && (!st->restart_flag || st->done)) return;
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < (int64_t)n + m; i += (int64_t)gridDim.x * kBlock) {
         if (i < n) {
-            chc[i] = ch[i] - (pb ? pa[i] + pb[i] : pa[i]);
+            chc[i] = ch[i] - ety[i];
         } else {
             const int64_t r = i - n;
-            bhc[r] = bh[r] - (qb ? qa[r] + qb[r] : qa[r]);
+            bhc[r] = bh[r] - (bhc[r] + ex[r]);
         }
     }
 }
@@ -1187,9 +1183,8 @@ hipError_t defect_refresh(pdhg_solver *s)
     row_product<float, double>(s, (const float *)s->aerr, xa, s->ex);
     col_product<float, double>(s, (const float *)s->aerr_t, ya, s->ety);
     const int g = grid_for((int64_t)s->n + s->m, kBlock, 8192);
-    hipLaunchKernelGGL(k_defect_set, dim3(g), dim3(kBlock), 0, st, s->n, s->m, s->st, 1, s->ch,
-                       (const double *)s->ety, (const double *)nullptr, s->chc, (const double *)s->bh,
-                       (const double *)s->bhc, (const double *)s->ex, s->bhc);
+    hipLaunchKernelGGL(k_defect_set, dim3(g), dim3(kBlock), 0, st, s->n, s->m, s->ch, s->ety, s->chc,
+                       (const double *)s->bh, s->ex, s->bhc);
     return hipGetLastError();
 }
 
