@@ -84,6 +84,7 @@ const double *cur_z(const pdhg_solver *s) { return s->dual_pushed ? s->zpush : s
 void free_all(pdhg_solver *s)
 {
     (void)push_compact_end(s, false);
+    setup_temps_end(s);
     void *ptrs[] = {s->slab,     s->feat_raw, s->feat_b,   s->logits,  s->lfix,          s->lcount,  s->sell_idx,
                     s->sell_val, s->sell_soff, s->sell_len, s->sell_wi_start, s->sell_wi, s->sell_part,
                     s->ypush,    s->zpush,    s->w0};
@@ -542,6 +543,7 @@ static int build_solver(int m, int n, int nz, const pdhg_params &p, const ModelS
         *s->st_host = hs;
         HIPCHK(hipMemcpyAsync(s->st, s->st_host, sizeof(DevState), hipMemcpyHostToDevice, st));
         HIPCHK(hipStreamSynchronize(st));
+        HIPCHK(setup_temps_begin(s));
         HIPCHK(build_transpose(s));
         HIPCHK(row_shapes(s));
         HIPCHK(scale_problem(s));
@@ -550,7 +552,10 @@ static int build_solver(int m, int n, int nz, const pdhg_params &p, const ModelS
             if (m > 0) HIPCHK(hipMemcpyAsync(s->bhc, s->bh, sizeof(double) * M, hipMemcpyDeviceToDevice, st));
         }
         if (s->kern_a == kRowSegs || (single && p.autotune)) HIPCHK(plan_row_segments(s));
-        if (s->kern_a == kSell) HIPCHK(sell_build(s, rp_host));
+        if (s->kern_a == kSell) {
+            setup_temps_end(s); // the layout may be many times the matrix: room for it
+            HIPCHK(sell_build(s, rp_host));
+        }
         if (single) {
             HIPCHK(resident_plan(s));
             HIPCHK(power_iteration(s));
@@ -561,6 +566,7 @@ static int build_solver(int m, int n, int nz, const pdhg_params &p, const ModelS
         }
         HIPCHK(hipMemcpyAsync(s->st_host, s->st, sizeof(DevState), hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
+        setup_temps_end(s);
         s->t_host = 0;
         s->next_check = p.check_every;
     } catch (const HipFailure &f) {

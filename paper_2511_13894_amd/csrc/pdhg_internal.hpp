@@ -26,7 +26,7 @@ namespace pdhg {
 // Several device arrays in one allocation.  Freeing an array of more than a
 // megabyte costs about 0.23 ms and allocating it 0.04 ms, whatever its size
 // (60 arrays of 20 MB: 13.9 and 1.7 ms; one of 1.2 GB: 0.30 and 0.08 ms), so a
-// solver's arrays, a phase's temporaries and the push model share one each.
+// solver's arrays, the set-up's temporaries and the push model share one each.
 class Slab {
 public:
     template <typename T>
@@ -39,12 +39,30 @@ public:
     hipError_t commit(void **base)
     {
         const hipError_t e = hipMalloc(base, total_ > 0 ? total_ : 1);
-        if (e == hipSuccess)
-            for (const auto &w : want_) *w.first = static_cast<char *>(*base) + w.second;
+        if (e == hipSuccess) place(*base);
         return e;
     }
+    // the arrays in an allocation that slabs use one after another, replaced if
+    // it is too small (then nothing may be at work on it)
+    hipError_t reuse(void **base, size_t *bytes)
+    {
+        if (!*base || total_ > *bytes) {
+            if (*base) (void)hipFree(*base);
+            *base = nullptr;
+            const hipError_t e = commit(base);
+            *bytes = e == hipSuccess ? total_ : 0;
+            return e;
+        }
+        place(*base);
+        return hipSuccess;
+    }
+    size_t bytes() const { return total_; }
 
 private:
+    void place(void *base)
+    {
+        for (const auto &w : want_) *w.first = static_cast<char *>(base) + w.second;
+    }
     std::vector<std::pair<void **, size_t>> want_;
     size_t total_ = 0;
 };
@@ -137,6 +155,8 @@ struct pdhg_solver {
     bool lone = false; // one LP of its own, not the model of a batch
     bool fp32 = false;
     void *slab = nullptr; // the arrays below that exist for every handle, in one allocation
+    void *setup_temps = nullptr; // temporaries of the set-up's phases, while it runs
+    size_t setup_bytes = 0;
 
     // original model, float64, row-compressed A and its explicit transpose
     int *rp = nullptr, *ci = nullptr;
@@ -361,6 +381,9 @@ struct BatchPart {
 // BAD_ROWPTR / BAD_COL); the rest is checked by ingest_device.
 hipError_t batch_assemble_device(hipStream_t st, const std::vector<BatchPart> &parts, int M, int N, int64_t NZ,
                                  DeviceModel *dm, std::vector<void *> &temps, unsigned *bad);
+// one allocation for the temporaries of the three below, and its end
+hipError_t setup_temps_begin(pdhg_solver *s);
+void setup_temps_end(pdhg_solver *s);
 hipError_t build_transpose(pdhg_solver *s);
 hipError_t scale_problem(pdhg_solver *s);
 hipError_t power_iteration(pdhg_solver *s);
