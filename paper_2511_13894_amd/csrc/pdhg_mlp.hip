@@ -502,11 +502,10 @@ __global__ __launch_bounds__(kBlock) void k_mlp_init(float *__restrict__ p, floa
 
 hipError_t mlp_init(pdhg_mlp *net, uint64_t seed)
 {
-    hipLaunchKernelGGL(k_mlp_init, dim3((MLP_NPARAMS + kBlock - 1) / kBlock), dim3(kBlock), 0, net->stream, net->p, net->m,
+    // on the pass stream, so that its first launch, which sets it up, is not a caller's
+    hipLaunchKernelGGL(k_mlp_init, dim3((MLP_NPARAMS + kBlock - 1) / kBlock), dim3(kBlock), 0, net->pass, net->p, net->m,
                        net->v, seed);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipStreamSynchronize(net->stream);
-    // on the pass stream, so that its first launch, which sets it up, is not a caller's
     if (e == hipSuccess) e = mlp_sync(net, net->pass);
     return e == hipSuccess ? hipStreamSynchronize(net->pass) : e;
 }
@@ -660,8 +659,6 @@ hipError_t mlp_pass_open(pdhg_mlp *net)
     std::lock_guard<std::mutex> lock(g_pass_mu);
     PassStream &p = g_pass[dev];
     if (!p.st && (e = hipStreamCreate(&p.st)) != hipSuccess) return e;
-    for (hipEvent_t &v : net->order)
-        if ((e = hipEventCreateWithFlags(&v, hipEventDisableTiming)) != hipSuccess) return e;
     p.users++;
     net->device = dev;
     net->pass = p.st;
@@ -679,6 +676,19 @@ void mlp_pass_close(pdhg_mlp *net)
     if (--p.users > 0) return;
     (void)hipStreamDestroy(p.st);
     p.st = nullptr;
+}
+
+hipError_t mlp_stream_open(pdhg_mlp *net)
+{
+    if (net->stream) return hipSuccess;
+    int dev = -1;
+    hipError_t e = hipGetDevice(&dev), e2 = hipSuccess;
+    if (e == hipSuccess && dev != net->device) e = hipSetDevice(net->device);
+    for (hipEvent_t &v : net->order)
+        if (e == hipSuccess && !v) e = hipEventCreateWithFlags(&v, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipStreamCreate(&net->stream);
+    if (dev >= 0 && dev != net->device) e2 = hipSetDevice(dev);
+    return e != hipSuccess ? e : e2;
 }
 
 hipError_t mlp_pass_wait(pdhg_mlp *net)

@@ -11,7 +11,7 @@
 #define MLP_NPARAMS 5313 // w1 (64x16), b1 (64), w2 (64x64), b2 (64), w3 (64), b3 (1)
 
 struct pdhg_mlp {
-    hipStream_t stream = nullptr;
+    hipStream_t stream = nullptr; // of calls that train or take host data, made with the first of them
     float *p = nullptr, *m = nullptr, *v = nullptr, *grad = nullptr; // float32 master values, Adam state
     short *w1b = nullptr, *w2b = nullptr, *w3b = nullptr;           // bfloat16 weight copies
     short *w2tb = nullptr;                                           // W2 transposed (the gradient kernel)
@@ -40,7 +40,9 @@ hipError_t mlp_train_step(pdhg_mlp *net, const short *F, const float *Y, const i
 // device address of the no-allocation forward's staging array on the current
 // device (looked up once per device)
 hipError_t mlp_scratch_setup();
-// take and give back the device's shared pass stream; wait for the passes on it (net->mu held)
+// the network's own stream (net->mu held); take and give back the device's shared pass
+// stream; wait for the passes on it (net->mu held)
+hipError_t mlp_stream_open(pdhg_mlp *net);
 hipError_t mlp_pass_open(pdhg_mlp *net);
 void mlp_pass_close(pdhg_mlp *net);
 hipError_t mlp_pass_wait(pdhg_mlp *net);

@@ -71,6 +71,7 @@ struct OwnStream {
     explicit OwnStream(pdhg_mlp *q) : net(q)
     {
         std::lock_guard<std::mutex> lock(net->mu);
+        CHK(mlp_stream_open(net));
         CHK(mlp_pass_wait(net));
         net->busy++;
     }
@@ -107,7 +108,6 @@ int pdhg_mlp_create(uint64_t seed, pdhg_mlp **out)
     pdhg_mlp *net = new (std::nothrow) pdhg_mlp();
     if (!net) return fail(PDHG_ERR_OOM, "host allocation failed");
     try {
-        CHK(hipStreamCreate(&net->stream));
         CHK(mlp_pass_open(net));
         for (float **q : {&net->p, &net->m, &net->v, &net->grad}) CHK(hipMalloc(q, sizeof(float) * MLP_NPARAMS));
         CHK(hipMalloc(&net->w1b, sizeof(short) * 1024));
@@ -120,7 +120,6 @@ int pdhg_mlp_create(uint64_t seed, pdhg_mlp **out)
         CHK(hipMalloc(&net->loss_acc, sizeof(double)));
         CHK(mlp_init(net, seed));
         CHK(mlp_scratch_setup()); // the no-allocation forward's staging array on this device
-        CHK(hipStreamSynchronize(net->stream));
     } catch (const HipFail &f) {
         pdhg_mlp_destroy(net);
         return hip_fail(f);
@@ -167,9 +166,11 @@ int pdhg_mlp_get_params(pdhg_mlp *net, float *params)
 {
     if (!net || !params) return fail(PDHG_ERR_INVALID_ARG, "NULL argument");
     try {
-        OwnStream own(net);
-        CHK(hipMemcpyAsync(params, net->p, sizeof(float) * MLP_NPARAMS, hipMemcpyDeviceToHost, net->stream));
-        CHK(hipStreamSynchronize(net->stream));
+        std::lock_guard<std::mutex> lock(net->mu);
+        hipStream_t st = net->busy ? net->stream : net->pass;
+        CHK(mlp_pass_wait(net));
+        CHK(hipMemcpyAsync(params, net->p, sizeof(float) * MLP_NPARAMS, hipMemcpyDeviceToHost, st));
+        CHK(hipStreamSynchronize(st));
     } catch (const HipFail &f) {
         return hip_fail(f);
     }
