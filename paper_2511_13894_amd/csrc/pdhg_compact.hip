@@ -213,8 +213,7 @@ int read_int(hipStream_t st, const int *p, hipError_t &e)
 
 void free_compact(pdhg_solver::PushCompact &c)
 {
-    for (void *q : c.slabs)
-        if (q) (void)hipFree(q);
+    for (void *q : c.slabs) (void)hipFree(q);
     c = pdhg_solver::PushCompact{};
 }
 
@@ -238,7 +237,7 @@ hipError_t begin_impl(pdhg_solver *s)
     flags.add(&c.newid, (size_t)n + 1);
     flags.add(&cnt, (size_t)(n > m ? n : m) + 1);
     flags.add(&tmp, scan);
-    if ((e = flags.commit(&c.slabs[0])) != hipSuccess) return e;
+    if ((e = flags.commit_small(&c.slabs)) != hipSuccess) return e;
     const int8_t *lfix = s->learned_active ? s->lfix : nullptr;
     hipLaunchKernelGGL((k_free_flags<V>), dim3(gn1), dim3(kBlock), 0, st, n, (const V *)s->lh, (const V *)s->uh, lfix,
                        c.flag);
@@ -256,7 +255,7 @@ hipError_t begin_impl(pdhg_solver *s)
     starts.add(&c.keep, (size_t)nf);
     starts.add(&c.tp, (size_t)nf + 1);
     starts.add(&c.rp, (size_t)m + 1);
-    if ((e = starts.commit(&c.slabs[1])) != hipSuccess) return e;
+    if ((e = starts.commit_small(&c.slabs)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_keep_list, dim3(gn1), dim3(kBlock), 0, st, n, c.flag, c.newid, c.keep);
     hipLaunchKernelGGL(k_col_len, dim3(grid_for((int64_t)nf + 1, kBlock, 1 << 30)), dim3(kBlock), 0, st, nf, c.keep,
                        s->tp, cnt);
@@ -292,7 +291,7 @@ hipError_t begin_impl(pdhg_solver *s)
         rest.add(&c.l, NF);
         rest.add(&c.u, NF);
     }
-    if ((e = rest.commit(&c.slabs[2])) != hipSuccess) return e;
+    if ((e = rest.commit_small(&c.slabs)) != hipSuccess) return e;
     hipLaunchKernelGGL((k_copy_cols<V>), dim3(grid_for(nf, kBlock, 1 << 30)), dim3(kBlock), 0, st, nf, c.keep, s->tp,
                        s->ti, (const V *)s->ahat_t, c.tp, c.ti, (V *)c.ahat_t);
     hipLaunchKernelGGL((k_copy_rows<V>), dim3(gw), dim3(kBlock), 0, st, m, s->rp, s->ci, (const V *)s->ahat, c.flag,
