@@ -99,7 +99,8 @@ typedef struct pdhg_params {
     int32_t precision;     /* enum pdhg_precision; default PDHG_FP64                    */
     double push_obj_scale; /* push objective = scale * Uniform[0,1); default 1          */
     int64_t push_max_iter; /* iteration cap of a push; default 1e6                      */
-    double time_limit;     /* seconds per solve / push call; <= 0: none (default)       */
+    double time_limit;     /* seconds per solve / push call, the clock read after every
+                              4 cycles of check_every; <= 0: none (default)           */
     void *stream;          /* hipStream_t; NULL: library-owned stream                   */
     int32_t verbosity;     /* 0 silent (default); > 0: kernel plans on stderr          */
     int32_t lanes_at;      /* primal-half kernel: 1..64 (power of 2) lanes per row;
@@ -118,8 +119,11 @@ typedef struct pdhg_params {
                               groups of one-wave workgroups with the tiles' sums        */
     int32_t lanes_a;       /* dual-half kernel, same encoding                           */
     int32_t use_graph;     /* 1: replay check cycles from a captured hipGraph (default) */
-    int32_t timing;        /* 1: time one primal and one dual launch per cycle with HIP
-                              events on the solver's stream (read by pdhg_get_timing)  */
+    int32_t timing;        /* 1: time one primal and one dual launch with HIP events on
+                              the solver's stream (read by pdhg_get_timing), in the
+                              first cycle of every group of cycles the host enqueues;
+                              that cycle launches its halves one by one, also for a
+                              small LP whose other cycles run in one workgroup         */
     int32_t autotune;      /* 1: at create, time every kernel choice of each half (such
                               tiles also as waves) on scratch vectors and keep the
                               fastest (0 = default: the
@@ -207,7 +211,9 @@ typedef struct pdhg_dual_push_result {
  * iteration kernels over the sampled launches of every solve and push call
  * since pdhg_create, and their algorithmic bytes per launch (matrix values,
  * indices and row pointers, one read of every vector the kernel reads, one
- * write of every vector it writes; gathers counted once). */
+ * write of every vector it writes; gathers counted once).  For a small LP,
+ * whose cycles otherwise run in one workgroup, they are those of the launched
+ * halves (about 3 us each), not what its iterations cost (1-4 us). */
 typedef struct pdhg_timing {
     double primal_ms;      /* mean duration of one primal-half launch (A'y + update) */
     double dual_ms;        /* mean duration of one dual-half launch (A xbar + update) */

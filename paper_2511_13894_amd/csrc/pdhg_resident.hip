@@ -12,7 +12,8 @@
 // launched kernels (they would not fit the registers either).  Measured, us
 // per iteration with the checks, launched -> resident, float64 / mixed: 200 x
 // 500 with 2,500 entries 6.3 -> 1.0 / 6.8 -> 1.1; 400 x 1,000 with 5,000 6.4 ->
-// 1.7 / 7.0 -> 2.0; 800 x 2,000 with 10,000 (mixed only) 7.0 -> 3.8;
+// 1.7 / 7.0 -> 2.0; 800 x 2,000 with 10,000 (mixed only) 7.0 -> 3.8 where no row
+// passes variant 3's 24 entries (four of ten such LPs; the others are launched);
 // transportation 40 x 100 with 8,000 entries 7.0 -> 2.6 / 6.7 -> 3.1.  A step of
 // the power iteration 13 us in six launches -> about 1 us.
 //
@@ -666,7 +667,8 @@ __global__ __launch_bounds__(kBlock) void k_longest(RowSegs sg, const int *__res
 // entries or of 256 rows of at most 4 (whose tiles then never pass one chunk
 // of entries, so the order is that of one chunk); rows in tiles of 256, 64 or
 // 32 rows, of at most one chunk of 2,048 entries, or in lane groups; and a
-// variant that holds the LP.
+// variant that holds the LP.  So one column of more than 8 entries, or a row past
+// a variant's entries a thread, sends an LP to the launched kernels.
 hipError_t resident_plan(pdhg_solver *s)
 {
     s->res = pdhg_solver::Resident{};

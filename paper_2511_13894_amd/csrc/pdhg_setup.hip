@@ -372,7 +372,7 @@ const char *ingest_error(unsigned bad)
 }
 
 // The temporaries of the set-up's phases.  They share one allocation: one of
-// each phase's own, of more than a megabyte where their arrays are smaller, took
+// each phase's own, of two megabytes and more where their arrays are smaller, took
 // 0.23 ms to free.  Create, ms, an allocation per array -> per phase -> one:
 // transportation 193 x 483 (186,000 entries) 1.42 -> 1.67 -> 1.08, 300 x 750 1.98 ->
 // 2.09 -> 1.26, power-law 10,000 x 40,000 2.67 -> 2.90 -> 2.36.
